@@ -56,6 +56,19 @@ __device__ __forceinline__ void lds_poison(void* p, int bytes)
 #endif
 }
 
+// Work-group barrier for data exchanged through LDS.  The wait for this wave's LDS accesses is
+// written out: the one that the fence of __syncthreads implies is dropped by the compiler where
+// the accesses sit in the predecessor of a loop header (clang 22: no lgkmcnt wait between the
+// staging writes at the end of an item and the barrier at the head of the next, in 140 of the FP64
+// tile kernels; the next item's reads can then pass the writes).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 #define AX_TRY(expr)              \
     do {                          \
         int _s = (expr);          \

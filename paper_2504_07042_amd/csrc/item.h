@@ -79,7 +79,7 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         const int64_t off = eb * EPB * 24 + q;
         svert[q] = off < m.E * 24 ? m.verts[off] : 0.0;
     }
-    __syncthreads();
+    lds_barrier();
     TriCoefT<T> tc;
     if (inslot) {
         const double* sv = svert + slot * 24;
@@ -108,7 +108,7 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
             for (int k = 0; k < N1; ++k) A[Shape<N1, sizeof(T)>::pos(i, j, k)] = xr[k];
         }
         contract<N1, false, true>(cs, xr, x2);
-        __syncthreads();
+        lds_barrier();
         T o1[N1];
         if (inslot) {
             T p[N1], o[N1];
@@ -132,12 +132,12 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
 #pragma unroll
             for (int k = 0; k < N1; ++k) lv[k] = lamp[(active ? e : 0) * NP + i + j * N1 + k * NT];
         }
-        __syncthreads();
+        lds_barrier();
         if (inslot) {
 #pragma unroll
             for (int a = 0; a < N1; ++a) A[Shape<N1, sizeof(T)>::pos(pa, a, pb)] = o1[a];
         }
-        __syncthreads();
+        lds_barrier();
         T tt[N1];
         if (inslot) {
 #pragma unroll
@@ -165,7 +165,7 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         }
         T y2[N1];
         contract<N1, true, true>(cs, tt, y2);
-        __syncthreads();
+        lds_barrier();
         if (inslot) {
             T p[N1], o[N1];
 #pragma unroll
@@ -177,17 +177,17 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
             for (int n = 0; n < N1; ++n) p[n] = A[Shape<N1, sizeof(T)>::pos(pa, n, pb)];
             contract<N1, true, true>(cs, p, o1);
         }
-        __syncthreads();
+        lds_barrier();
         if (inslot) {
 #pragma unroll
             for (int a = 0; a < N1; ++a) B[Shape<N1, sizeof(T)>::pos(pa, a, pb)] += o1[a];
         }
-        __syncthreads();
+        lds_barrier();
         if (active) {
 #pragma unroll
             for (int k = 0; k < N1; ++k) Y[base + i + j * N1 + k * NT] = B[Shape<N1, sizeof(T)>::pos(i, j, k)] + y2[k];
         }
-        __syncthreads();
+        lds_barrier();
     }
 }
 
