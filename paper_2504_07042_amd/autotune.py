@@ -41,14 +41,17 @@ KNOBS = ("kernel", "tile_alt", "item_alt", "waves_alt", "grid_mult")
 DEFAULT = {"kernel": AX_KERNEL_AUTO, "tile_alt": 0, "item_alt": 0, "waves_alt": 0, "grid_mult": 2}
 GRID_MULTS = (1, 2, 4, 8)
 MARGIN = 0.01      # a variant replaces the default only if it is this much faster
+KERNEL_MARGIN = 0.05   # single-mesh forms: another kernel than the default's, only if this much faster
+                       # than the default kernel's best variant (between the two kernels repeat runs
+                       # differ by up to 5 % at the orders where they tie)
 
 
 # The sources the tuned launches depend on: the AxLocal kernels (tile, per-item, batched), their
 # shared headers, the dispatch and the tuning table.  The solver, gather-scatter, set-up and probe
 # sources do not change what the tuner times.
 TUNED_SOURCES = ("ax_internal.h", "ax_kernels.h", "geom.h", "ax_local_impl.h", "ax_local_f64.hip",
-                 "ax_local_f32.hip", "item.h", "item_f64.hip", "item_f32.hip", "batched.hip", "ax_local.hip",
-                 "ax_common.cpp")
+                 "ax_local_f64_geo.hip", "ax_local_f32.hip", "ax_local_f32_geo.hip", "item.h",
+                 "item_f64.hip", "item_f32.hip", "batched.hip", "ax_local.hip", "ax_common.cpp")
 
 
 def source_hash() -> str:
@@ -239,6 +242,13 @@ def tune(orders=range(1, 16), kinds=tuple(KINDS), precs=tuple(PRECS), target_nod
                     times = [t / ncol for t in times]   # per column, as ndof counts one
                     t_def = times[0]
                 q = min(range(len(cands)), key=lambda i: times[i])
+                if kname in ("trilinear", "partial"):
+                    tune_set(N, kind, prec, **DEFAULT)
+                    own_kernel = tune_get(N, kind, prec)["kernel_used"]
+                    own = [i for i, c in enumerate(cands) if i == 0 or c["kernel"] == own_kernel]
+                    qo = min(own, key=lambda i: times[i])
+                    if times[q] > (1.0 - KERNEL_MARGIN) * times[qo]:
+                        q = qo
                 chosen = cands[q] if times[q] < (1.0 - MARGIN) * t_def else cands[0]
                 t_best = times[q] if chosen is cands[q] else t_def
                 tune_set(N, kind, prec, **chosen)

@@ -29,11 +29,11 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
 
-SOURCES = ["ax_common.cpp", "ax_local.hip", "ax_local_f64.hip", "ax_local_f32.hip", "ax_local_f16.hip",
-           "item_f64.hip", "item_f32.hip", "ax_setup.hip", "gs.hip", "cg.hip", "batched.hip", "probe.hip"]
+SOURCES = ["ax_common.cpp", "ax_local.hip", "ax_local_f64.hip", "ax_local_f64_geo.hip", "ax_local_f32.hip",
+           "ax_local_f32_geo.hip", "ax_local_f16.hip", "item_f64.hip", "item_f32.hip", "ax_setup.hip", "gs.hip", "cg.hip", "batched.hip", "probe.hip"]
 # sources whose kernels hold LDS arrays: recompiled for the poisoned debug twin
-LDS_SOURCES = ["ax_local_f64.hip", "ax_local_f32.hip", "ax_local_f16.hip", "item_f64.hip", "item_f32.hip",
-               "batched.hip"]
+LDS_SOURCES = ["ax_local_f64.hip", "ax_local_f64_geo.hip", "ax_local_f32.hip", "ax_local_f32_geo.hip",
+               "ax_local_f16.hip", "item_f64.hip", "item_f32.hip", "batched.hip"]
 
 
 def _compile(job) -> str:

@@ -112,17 +112,6 @@ constexpr bool item_available(int N1, int geo)
     return (geo == GEO_TRI && N1 >= 2 && N1 <= 16) || (geo == GEO_TRIL && N1 >= 9 && N1 <= 16);
 }
 
-// Tuning knobs (compile-time): waves per SIMD the register allocation targets for N1 <= 8, and
-// how many times the resident capacity the persistent grid is.
-#ifndef AX_MINW_SMALL
-#define AX_MINW_SMALL 4
-#endif
-#ifndef AX_MINW_OTHER
-#define AX_MINW_OTHER 2
-#endif
-#ifndef AX_PERSIST_MULT
-#define AX_PERSIST_MULT 2
-#endif
 // XOR-swizzled LDS layout for N1 = 8 (no padding; conflict-free for the home, r-pencil and
 // s-pencil access patterns) instead of the padded row stride.
 #ifndef AX_LDS_SWIZZLE
@@ -184,41 +173,28 @@ struct Shape {
     static constexpr int EPB_ALT = N1 == 2 ? 32 : N1 == 3 ? 14 : N1 == 4 ? 8 : N1 == 5 ? 10
                                  : N1 == 6 ? 14 : N1 == 7 ? 10 : N1 == 8 ? 2 : N1 <= 11 ? 1 : EPB;
     static constexpr int BLOCK = ((EPB * NT + 63) / 64) * 64;
-    static constexpr int SLOTS = (BLOCK + NT - 1) / NT;
-    // waves per SIMD the register allocation must allow (latency hiding for the X/Y streams)
-    static constexpr int MINW = N1 == 8 ? AX_MINW_SMALL : AX_MINW_OTHER;
 };
 
-// Waves per SIMD the register allocation of the prefetching (tile) kernel targets: four at
-// N1 = 8 and two elsewhere (AX_MINW_SMALL / AX_MINW_OTHER), except that the FP64 Helmholtz kernel
-// at N1 = 8 also carries the mass-term operands through the last phases, which does not fit the
-// four-wave budget without spills, and FP32 at N1 = 8, measured interleaved at N = 7, 32^3 with
-// LDS layout 2: the trilinear kernel is fastest at four (49.3 us; five spill 6 registers,
-// 52.0 us; six 58.2 us), partial recomputation at five (47.0 vs 48.6 us at four),
-// parallelepipeds and stored factors within 1 % of each other from four to six.
-#ifndef AX_HELM_MINW
-#define AX_HELM_MINW 3
+// Waves per SIMD the register allocation of the prefetching (tile) kernel must allow: the most at
+// which a single-column kernel does not spill (a few registers at N1 = 4 and FP32 aside).  FP64:
+// four to N1 = 8, three above (natural use 110-168 VGPRs; 9 and 10 then run four), two for the
+// Helmholtz form from N1 = 12 (184-224 VGPRs, 15-60 spills at three).  N1 = 16 is held to two by
+// its LDS.  FP32: five (96 VGPRs) except the trilinear and Helmholtz forms to N1 = 12, four.
+#ifndef AX_MINW_F64_LO
+#define AX_MINW_F64_LO 4
 #endif
-#ifndef AX_MINW_F32
-#define AX_MINW_F32 5
+#ifndef AX_MINW_F64_HI
+#define AX_MINW_F64_HI 3
 #endif
 #ifndef AX_MINW_F32_TRI
 #define AX_MINW_F32_TRI 4
 #endif
-#ifndef AX_MINW_TINY
-#define AX_MINW_TINY AX_MINW_OTHER
-#endif
-#ifndef AX_MINW_MID
-#define AX_MINW_MID AX_MINW_OTHER
-#endif
 constexpr int tile_waves(int N1, int geo, bool fp32)
 {
-    return (geo == GEO_HELM && N1 == 8 && !fp32) ? AX_HELM_MINW
-           : (N1 == 8 && fp32)                  ? (geo == GEO_TRI ? AX_MINW_F32_TRI : AX_MINW_F32)
-           : N1 == 8                            ? AX_MINW_SMALL
-           : N1 <= 4                            ? AX_MINW_TINY
-           : N1 <= 7                            ? AX_MINW_MID
-                                                : AX_MINW_OTHER;
+    if (N1 == 16) return 2;
+    if (fp32) return (geo == GEO_TRI || geo == GEO_HELM) && N1 <= 12 ? AX_MINW_F32_TRI : 5;
+    if (N1 <= 8) return geo == GEO_HELM && N1 == 4 ? 3 : AX_MINW_F64_LO;
+    return geo == GEO_HELM && N1 >= 12 ? 2 : AX_MINW_F64_HI;
 }
 
 // Coefficient sources of the contractions.  CoefResident reads the basis tables as they are
@@ -279,6 +255,166 @@ struct CoefConst {
     __device__ __forceinline__ double xi(int q) const { return k->xi[q]; }
     __device__ __forceinline__ double w(int q) const { return k->w[q]; }
 };
+
+// ---- FP64 contractions with row-broadcast coefficients ----
+//
+// The even-odd blocks of an order do not fit the scalar register file from N1 = 10 on (2 H^2
+// doubles against about 50), so scalar sources reload them row by row: scalar loads in every
+// contraction whose waits also drain the LDS counter, and lane spills of what stays resident.
+// A vector register instead holds 16 coefficients, one per lane of each 16-lane row, and
+// v_fmac_f64 takes one of them for the whole row as a row_newbcast operand: the tables of N1 = 16
+// are 8 such registers, no scalar load is left in the loop, and the multiply-add issues at the
+// full FP64 rate (measured over 8 independent chains: 72.4 TF/s with a row-broadcast operand,
+// 73.3 with a scalar one; FP32 halves its rate with one, so FP32 keeps the scalar sources).
+// Every lane of the wave must be active: a broadcast reads the lanes of its own row.
+//
+// Coefficient q of an order: P[a][n] at a H + n, M[a][n] at H^2 + a H + n, then Cm[a], Rm[n];
+// register q / 16, lane q % 16.
+template <int N1>
+struct DppCoef {
+    static constexpr int H = N1 / 2;
+    static constexpr int P0 = 0, M0 = H * H, C0 = 2 * H * H, R0 = C0 + H;
+    static constexpr int COUNT = 2 * H * H + (N1 % 2 ? 2 * H : 0);
+    static constexpr int REGS = (COUNT + 15) / 16;
+    double r[REGS];
+};
+
+// Loads this lane's coefficients from the tables in global or constant memory.
+template <int N1, typename B>
+__device__ __forceinline__ void dpp_coef_init(const B& bs, int lane, DppCoef<N1>& k)
+{
+    using K = DppCoef<N1>;
+    const int l = lane & 15;
+#pragma unroll
+    for (int g = 0; g < K::REGS; ++g) {
+        const int q = 16 * g + l;
+        double v = 0.0;
+        if (q < K::M0) v = bs.P[q];
+        else if (q < K::C0) v = bs.M[q - K::M0];
+        else if (q < K::COUNT) v = q < K::R0 ? bs.Cm[q - K::C0] : bs.Rm[q - K::R0];
+        k.r[g] = v;
+    }
+}
+
+// e += sum over T terms of coefficient EQ(i) times ue[i], o likewise: the two chains interleaved.
+// The s_nop covers the two wait states a row-broadcast read needs after a vector write of its
+// register (the compiler may have just copied a coefficient there).
+#define AX_DPP_FMAC(acc, c, x, l) "v_fmac_f64_dpp " acc ", " c ", " x " row_newbcast:" l " row_mask:0xf bank_mask:0xf\n\t"
+
+template <int T, int EQ0, int ES, int OQ0, int OS, typename K>
+__device__ __forceinline__ void dpp_terms(const K& k, const double* ue, const double* uo, double& e, double& o)
+{
+    static_assert(T >= 1 && T <= 4, "terms per block");
+#define AX_EC(i) "v"(k.r[(EQ0 + (i) * ES) / 16])
+#define AX_OC(i) "v"(k.r[(OQ0 + (i) * OS) / 16])
+#define AX_EL(i) "n"((EQ0 + (i) * ES) % 16)
+#define AX_OL(i) "n"((OQ0 + (i) * OS) % 16)
+    if constexpr (T == 1)
+        asm("s_nop 1\n\t" AX_DPP_FMAC("%0", "%2", "%4", "%6") AX_DPP_FMAC("%1", "%3", "%5", "%7")
+            : "+v"(e), "+v"(o)
+            : AX_EC(0), AX_OC(0), "v"(ue[0]), "v"(uo[0]), AX_EL(0), AX_OL(0));
+    else if constexpr (T == 2)
+        asm("s_nop 1\n\t" AX_DPP_FMAC("%0", "%2", "%6", "%10") AX_DPP_FMAC("%1", "%3", "%7", "%11")
+            AX_DPP_FMAC("%0", "%4", "%8", "%12") AX_DPP_FMAC("%1", "%5", "%9", "%13")
+            : "+v"(e), "+v"(o)
+            : AX_EC(0), AX_OC(0), AX_EC(1), AX_OC(1), "v"(ue[0]), "v"(uo[0]), "v"(ue[1]), "v"(uo[1]), AX_EL(0),
+              AX_OL(0), AX_EL(1), AX_OL(1));
+    else if constexpr (T == 3)
+        asm("s_nop 1\n\t" AX_DPP_FMAC("%0", "%2", "%8", "%14") AX_DPP_FMAC("%1", "%3", "%9", "%15")
+            AX_DPP_FMAC("%0", "%4", "%10", "%16") AX_DPP_FMAC("%1", "%5", "%11", "%17")
+            AX_DPP_FMAC("%0", "%6", "%12", "%18") AX_DPP_FMAC("%1", "%7", "%13", "%19")
+            : "+v"(e), "+v"(o)
+            : AX_EC(0), AX_OC(0), AX_EC(1), AX_OC(1), AX_EC(2), AX_OC(2), "v"(ue[0]), "v"(uo[0]), "v"(ue[1]),
+              "v"(uo[1]), "v"(ue[2]), "v"(uo[2]), AX_EL(0), AX_OL(0), AX_EL(1), AX_OL(1), AX_EL(2), AX_OL(2));
+    else
+        asm("s_nop 1\n\t" AX_DPP_FMAC("%0", "%2", "%10", "%18") AX_DPP_FMAC("%1", "%3", "%11", "%19")
+            AX_DPP_FMAC("%0", "%4", "%12", "%20") AX_DPP_FMAC("%1", "%5", "%13", "%21")
+            AX_DPP_FMAC("%0", "%6", "%14", "%22") AX_DPP_FMAC("%1", "%7", "%15", "%23")
+            AX_DPP_FMAC("%0", "%8", "%16", "%24") AX_DPP_FMAC("%1", "%9", "%17", "%25")
+            : "+v"(e), "+v"(o)
+            : AX_EC(0), AX_OC(0), AX_EC(1), AX_OC(1), AX_EC(2), AX_OC(2), AX_EC(3), AX_OC(3), "v"(ue[0]), "v"(uo[0]),
+              "v"(ue[1]), "v"(uo[1]), "v"(ue[2]), "v"(uo[2]), "v"(ue[3]), "v"(uo[3]), AX_EL(0), AX_OL(0), AX_EL(1),
+              AX_OL(1), AX_EL(2), AX_OL(2), AX_EL(3), AX_OL(3));
+#undef AX_EC
+#undef AX_OC
+#undef AX_EL
+#undef AX_OL
+}
+
+// one chain: m += coefficient MQ times x
+template <int MQ, typename K>
+__device__ __forceinline__ void dpp_term(const K& k, double x, double& m)
+{
+    asm("s_nop 1\n\t" AX_DPP_FMAC("%0", "%1", "%2", "%3") : "+v"(m) : "v"(k.r[MQ / 16]), "v"(x), "n"(MQ % 16));
+}
+
+// terms N0..H-1 of one output row, four at a time (coefficients EQ0 + n ES and OQ0 + n OS)
+template <int H, int N0, int EQ0, int ES, int OQ0, int OS, typename K>
+__device__ __forceinline__ void dpp_row(const K& k, const double* ue, const double* uo, double& e, double& o)
+{
+    if constexpr (N0 < H) {
+        constexpr int T = H - N0 >= 4 ? 4 : H - N0;
+        dpp_terms<T, EQ0 + N0 * ES, ES, OQ0 + N0 * OS, OS>(k, ue + N0, uo + N0, e, o);
+        dpp_row<H, N0 + T, EQ0, ES, OQ0, OS>(k, ue, uo, e, o);
+    }
+}
+
+// Orders whose first coefficient of every row also fits the scalar registers (4 H doubles): the
+// row's chains then start with a product instead of a cleared accumulator.
+template <int N1>
+constexpr bool dpp_scalar_start() { return N1 <= 9; }
+
+template <int N1, bool TRANS, int A, typename B>
+__device__ __forceinline__ void dpp_rows(const DppCoef<N1>& k, const B& bs, const double* in, const double* ue,
+                                         const double* uo, double* out)
+{
+    using K = DppCoef<N1>;
+    constexpr int H = K::H, N = N1 - 1;
+    if constexpr (A < H) {
+        constexpr int S = dpp_scalar_start<N1>() ? 1 : 0;
+        double e = 0.0, o = 0.0;
+        if constexpr (S == 1) {
+            e = (TRANS ? bs.M[A] : bs.P[A * H]) * ue[0];
+            o = (TRANS ? bs.P[A] : bs.M[A * H]) * uo[0];
+        }
+        if constexpr (TRANS)
+            dpp_row<H, S, K::M0 + A, H, K::P0 + A, H>(k, ue, uo, e, o);
+        else
+            dpp_row<H, S, K::P0 + A * H, 1, K::M0 + A * H, 1>(k, ue, uo, e, o);
+        if constexpr (N1 % 2 == 1) dpp_term<(TRANS ? K::R0 : K::C0) + A>(k, in[H], e);
+        out[A] = e + o;
+        out[N - A] = o - e;
+        dpp_rows<N1, TRANS, A + 1>(k, bs, in, ue, uo, out);
+    }
+}
+
+template <int N1, bool TRANS, int A>
+__device__ __forceinline__ void dpp_middle(const DppCoef<N1>& k, const double* uo, double& m)
+{
+    using K = DppCoef<N1>;
+    if constexpr (A < K::H) {
+        dpp_term<(TRANS ? K::C0 : K::R0) + A>(k, uo[A], m);
+        dpp_middle<N1, TRANS, A + 1>(k, uo, m);
+    }
+}
+
+// contract_eo (below) in FP64 with row-broadcast coefficients: the same operations in the same
+// order, so the same bits.
+template <int N1, bool TRANS, typename B>
+__device__ __forceinline__ void contract_dpp(const DppCoef<N1>& k, const B& bs, const double* in, double* out)
+{
+    constexpr int H = N1 / 2, N = N1 - 1;
+    double ue[H], uo[H];
+#pragma unroll
+    for (int n = 0; n < H; ++n) {
+        ue[n] = in[n] + in[N - n];
+        uo[n] = in[n] - in[N - n];
+    }
+    double m = 0.0;
+    if constexpr (N1 % 2 == 1) dpp_middle<N1, TRANS, 0>(k, uo, m);
+    dpp_rows<N1, TRANS, 0>(k, bs, in, ue, uo, out);
+    if constexpr (N1 % 2 == 1) out[H] = m;
+}
 
 // Basis member `bs` of the kernel's single by-value argument struct KA.
 template <typename T, typename KA>
@@ -347,71 +483,6 @@ __device__ __forceinline__ void contract_eo(const C& src, const T* in, T* out)
 #pragma unroll
         for (int n = 0; n < H; ++n) m = fma(TRANS ? c.Cm(n) : c.Rm(n), uo[n], m);
         out[H] = m;
-    }
-}
-
-// ---- FP32 contractions on the matrix cores ----
-//
-// v_mfma_f32_4x4x1f32 runs 16 independent 4x4 outer products per wave: block b = lane / 4 forms
-// acc_b[i][j] += a(lane 4b + i) * b(lane 4b + j) and lane 4b + j receives acc_b[i][j] in its
-// register i.  With b = a lane's own pencil value in[n] and a = C[4g + (lane % 4)][n] (a per-lane
-// coefficient register), N1 such instructions leave out[4g + i] of the lane's OWN pencil in
-// register i: the pencil contraction of the vector-unit code, in the same lane layout, with no
-// re-layout and no vector-ALU work.  A centro-antisymmetric C (C[N-a][N-n] = -C[a][n], which D
-// and D^T of GLL points are) gives the rows a >= N1/2 from the rows below through the reversed
-// pencil: sum_m C[a][m] in[N-m] = -out[N-a], so one set of coefficient registers (rows
-// 0..N1/2-1) serves all rows.  Even N1 only (an odd order's middle row would need its own set).
-typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-
-template <int N1>
-struct MfmaCoef {
-    static constexpr int H = N1 / 2;
-    static constexpr int G = (H + 3) / 4;  // groups of four output rows
-    float c[G][N1];                        // C[4g + lane % 4][n] (0 past row H-1)
-};
-
-// Coefficient registers of this lane for C = D (TRANS = false) or C = D^T, from the basis table.
-template <int N1, bool TRANS, typename B>
-__device__ __forceinline__ void mfma_coef_init(const B& bs, int lane, MfmaCoef<N1>& k)
-{
-    const int r = lane & 3;
-#pragma unroll
-    for (int g = 0; g < MfmaCoef<N1>::G; ++g)
-#pragma unroll
-        for (int n = 0; n < N1; ++n) {
-            float v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int a = 4 * g + q;
-                v[q] = a < MfmaCoef<N1>::H ? float(TRANS ? bs.D[n * N1 + a] : bs.D[a * N1 + n]) : 0.0f;
-            }
-            k.c[g][n] = r == 0 ? v[0] : r == 1 ? v[1] : r == 2 ? v[2] : v[3];
-        }
-}
-
-// out = C in for this lane's pencil (every lane of the wave must execute it: the matrix-core
-// instruction works on whole waves).
-template <int N1>
-__device__ __forceinline__ void contract_mfma(const MfmaCoef<N1>& k, const float* in, float* out)
-{
-    static_assert(N1 % 2 == 0, "matrix-core contraction: even N1");
-    constexpr int H = N1 / 2, N = N1 - 1;
-#pragma unroll
-    for (int g = 0; g < MfmaCoef<N1>::G; ++g) {
-        mfma_f4 acc = {0.f, 0.f, 0.f, 0.f}, rev = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int n = 0; n < N1; ++n) {
-            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(k.c[g][n], in[n], acc, 0, 0, 0);
-            rev = __builtin_amdgcn_mfma_f32_4x4x1f32(k.c[g][n], in[N - n], rev, 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int a = 4 * g + q;
-            if (a < H) {
-                out[a] = acc[q];
-                out[N - a] = -rev[q];
-            }
-        }
     }
 }
 

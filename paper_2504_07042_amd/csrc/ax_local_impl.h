@@ -32,31 +32,7 @@
 #ifndef AX_XW_SCALAR
 #define AX_XW_SCALAR 1
 #endif
-// 1: the trilinear per-element prelude runs at the start of each item (fewest live registers);
-// 0: between the forward r/s contractions and the pointwise stage.
-#ifndef AX_EARLY_PRELUDE
-#define AX_EARLY_PRELUDE 1
-#endif
-// 1: the s-direction transpose contraction goes back to LDS in place and the output stage sums
-// the two fields (one barrier and one read-modify-write pass fewer); 0: it is added into the
-// r-field through a separate pass.
-#ifndef AX_MERGE_RS
-#define AX_MERGE_RS 1
-#endif
-
-// 1: the FP32 N1 = 8 kernels run their D-contractions on the matrix cores (contract_mfma, 96
-// v_mfma_f32_4x4x1f32 per element instead of 288 vector instructions); 0: on the vector ALU.
-// Measured interleaved on gfx950 (trilinear, N = 7, 32^3): 65.8 us with the matrix cores against
-// 52.0 us on the vector ALU, i.e. each 4x4x1 instruction costs about as much issue time as the
-// vector work it replaces plus register pressure (128 VGPRs and spills); so 0.
-#ifndef AX_F32_MFMA
-#define AX_F32_MFMA 0
-#endif
-
 namespace ax {
-
-template <int N1, bool EO, typename T>
-constexpr bool use_mfma() { return AX_F32_MFMA && EO && sizeof(T) == 4 && N1 == 8; }
 
 // Work-group shape for EPBX elements of order N1 - 1.
 template <int N1, int EPBX>
@@ -64,7 +40,7 @@ struct Tile {
     static constexpr int NT = N1 * N1;
     static constexpr int EPB = EPBX;
     static constexpr int BLOCK = ((EPB * NT + 63) / 64) * 64;
-    static constexpr int SLOTS = (BLOCK + NT - 1) / NT;
+    static constexpr bool FULL = EPB * NT == BLOCK;  // no idle lanes
 };
 
 // Kernel argument block (one by-value struct, so that the contraction tables can also be read
@@ -84,16 +60,25 @@ struct AxArgs {
     Basis<T> bs;
 };
 
-// Orders whose contraction tables are read per output row instead of held in scalar registers.
-// (measured on gfx950: the FP64 trilinear kernel at N1 = 10 is faster with resident tables)
-template <int N1, int GEO, typename T>
-constexpr bool reload_coefs() { return sizeof(T) == 8 ? N1 >= (is_trilinear(GEO) ? 11 : 10) : N1 >= 13; }
+// FP64 kernels whose even-odd tables are held in vector registers and broadcast (contract_dpp):
+// the orders whose tables overflow the scalar registers (N1 >= 9), and the multi-column trilinear
+// kernels at N1 = 4 and 8, which spill with scalar tables (30 and 99 VGPRs at four waves per SIMD,
+// none with broadcast ones).  Elsewhere the scalar tables are the faster source: no accumulator
+// has to be cleared first (one move per output, 6 % of the vector work at N1 = 8).
+template <int N1, int GEO, bool EO, bool ONE, typename T>
+constexpr bool use_dpp()
+{
+    return EO && sizeof(T) == 8 && (N1 >= 9 || (is_trilinear(GEO) && (N1 == 8 || (!ONE && N1 == 4))));
+}
 
+// Orders whose contraction tables are read per output row instead of held in scalar registers.
+template <int N1, bool EO, typename T>
+constexpr bool reload_coefs() { return sizeof(T) == 8 ? !EO && N1 >= 10 : N1 >= 13; }
 // (xi_k, w_k) of node k for the pointwise stage
 template <int N1, int GEO, bool EO, typename T, typename B>
 __device__ __forceinline__ void node_xw(const B& bs, const double* sxw, int k, T& t, T& wk)
 {
-    if constexpr (EO && AX_XW_SCALAR && !reload_coefs<N1, GEO, T>()) {
+    if constexpr (EO && AX_XW_SCALAR && !reload_coefs<N1, EO, T>()) {
         const int m = k < N1 - 1 - k ? k : N1 - 1 - k;
         const double x = bs.xi[m];
         t = T(k == m ? x : -x);
@@ -111,6 +96,48 @@ __device__ __forceinline__ P* at_bytes(P* base, uint32_t off)
 {
     using C = typename std::conditional<std::is_const<P>::value, const char, char>::type;
     return reinterpret_cast<P*>(reinterpret_cast<C*>(base) + off);
+}
+
+// Global memory behind a work-group-uniform base, reached with a 32-bit lane offset `lo` plus a
+// compile-time byte offset.  Buffer accesses take the base from scalar registers, the lane offset
+// from one vector register and the rest as a scalar offset, however far it reaches; global
+// accesses have 4 KB of immediate offset, beyond which the compiler keeps one 64-bit lane address
+// per node in vector registers over the whole loop (48 of them at N1 = 12).
+struct Buf {
+    __amdgpu_buffer_rsrc_t r;
+    // valid = false: every load returns 0 and touches no memory
+    __device__ __forceinline__ explicit Buf(const void* base, bool valid = true)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, valid ? 0x7fffffff : 0, 0x00027000))
+    {
+    }
+    template <int OFF, typename T>
+    __device__ __forceinline__ T load(uint32_t lo) const
+    {
+        if constexpr (sizeof(T) == 8)
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lo, OFF, 0));
+        else
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lo, OFF, 0));
+    }
+    template <int OFF, typename T>
+    __device__ __forceinline__ void store(uint32_t lo, T v) const
+    {
+        if constexpr (sizeof(T) == 8) {
+            typedef unsigned u2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lo, OFF, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lo, OFF, 0);
+        }
+    }
+};
+
+// f(integral constant k) for k = 0..N1-1
+template <int N1, int K = 0, typename F>
+__device__ __forceinline__ void each_node(F&& f)
+{
+    if constexpr (K < N1) {
+        f(std::integral_constant<int, K>{});
+        each_node<N1, K + 1>(static_cast<F&&>(f));
+    }
 }
 
 // The r-pencil (., j, k) of a field: contiguous words i = 0..N1-1.  With layout 2 every pencil
@@ -185,6 +212,14 @@ constexpr int s_hoist()
     if constexpr (N1 == 8 && sizeof(T) == 8 && GEO == GEO_TRI) return AX_S_HOIST_F64_TRI;
     return N1 == 8 && (sizeof(T) == 4 ? (GEO == GEO_TRI || GEO == GEO_PARA) : GEO == GEO_TRIL) ? 3 : 0;
 }
+// Where the next item's loads are issued.  Trilinear forms, and every form from N1 = 9: after the
+// pointwise stage and the t-contraction of its result, when the factor coefficients and x2 are
+// dead, so that the prefetched column adds nothing to the register peak (FP64 N1 = 12: 134 VGPRs
+// against 216 with the loads at the start of the item).  Parallelepipeds and stored factors up to
+// N1 = 8 fit the registers with the loads after the first contraction, which measured 2-5 % faster
+// there (a longer time in flight).
+template <int N1, int GEO>
+constexpr bool late_prefetch() { return is_trilinear(GEO) || N1 >= 9; }
 template <int BLOCK>
 __device__ __forceinline__ void group_sync()
 {
@@ -192,6 +227,8 @@ __device__ __forceinline__ void group_sync()
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // the scheduler keeps the phases apart as it does across a hardware barrier
+        __builtin_amdgcn_sched_barrier(0);
     } else {
         lds_barrier();
     }
@@ -221,7 +258,7 @@ struct OneMeshWalk {
 // es = nrhs N1^3, ccs = N1^3 for the component-interleaved [E][nrhs][N1^3] of a vector field).
 // With a work list `wl` (W::kList, trilinear only, es = N1^3) the element groups and their
 // addresses come from the list; E, geo, X, Y, l2g, ldg and ccs are then unused.
-template <int N1, int GEO, bool EO, int GATHER, int EPBX, typename T, typename C, typename W = OneMeshWalk>
+template <int N1, int GEO, bool EO, int GATHER, int EPBX, bool ONE, typename T, typename C, typename W = OneMeshWalk>
 __device__ __forceinline__ void
 ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __restrict__ Gs,
               const T* __restrict__ X, T* __restrict__ Y, const Basis<T>& bs,
@@ -233,10 +270,12 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     using TL = Tile<N1, EPBX>;
     constexpr int NT = S::NT, FS = S::FS, NP = S::NP, EPB = TL::EPB;
     constexpr int BLOCK = TL::BLOCK;
-    constexpr int NV = is_trilinear(GEO) ? 24 : 0;               // vertex words per element
-    constexpr int VPT = (EPB * NV + BLOCK - 1) / BLOCK;          // vertex words per thread
-    __shared__ __attribute__((aligned(16))) T smem[TL::SLOTS * 2 * FS];
-    __shared__ double svert[is_trilinear(GEO) ? EPB * 24 : 1];
+    constexpr int NV = is_trilinear(GEO) ? 24 : GEO == GEO_PARA ? 6 : 0;   // geometry words per element
+    constexpr int VPT = (EPB * NV + BLOCK - 1) / BLOCK;          // and per thread
+    __shared__ __attribute__((aligned(16))) T smem[EPB * 2 * FS];
+    // trilinear: the monomial coefficients of the map, [element][coordinate][monomial];
+    // parallelepiped: h
+    __shared__ __attribute__((aligned(16))) double svert[NV > 0 ? EPB * NV : 1];
     // (xi_k, w_k) pairs: the per-lane (xi_i, w_i), (xi_j, w_j) of the home columns, and xi_k, w_k
     // of the node loop for the kernels that do not keep them in scalar registers
     __shared__ double sxw[2 * N1];
@@ -248,10 +287,16 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
 
     const int tid = threadIdx.x;
     if constexpr (GATHER == 2) sen[tid] = 0.0;
-    const int slot = (TL::SLOTS == 1) ? 0 : tid / NT;
+    const int slot = (EPB == 1 && TL::FULL) ? 0 : tid / NT;
     const int lane = tid - slot * NT;
-    T* __restrict__ A = smem + slot * 2 * FS;
-    T* __restrict__ B = A + FS;
+    // lanes past the last slot read slot 0's fields and write nothing
+    const bool inslot = TL::FULL || slot < EPB;
+    T* __restrict__ A = smem + (inslot ? slot : 0) * 2 * FS;
+    // the second field's base in its own register: as an offset from the first it leaves the reach
+    // of the paired LDS accesses and costs one address register per pair
+    int bo = (inslot ? slot : 0) * 2 * FS + FS;
+    asm("" : "+v"(bo));
+    T* __restrict__ B = smem + bo;
     const int i = lane % N1, j = lane / N1;    // home lane: node column (i, j, :)
     const int pa = S::spa(lane), pb = S::spb(lane);  // s-pencil lane (i, k)
     const int ra = S::rpa(lane), rb = S::rpb(lane);  // r-pencil lane (j, k)
@@ -262,22 +307,20 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         nblk = (E + EPB - 1) / EPB;
     if (tid < 2 * N1) sxw[tid] = (tid & 1) ? bs.w[tid >> 1] : bs.xi[tid >> 1];
     group_sync<BLOCK>();   // sxw is read by every wave from the first element on
-    // the D-contractions: forward (D) and transposed (D^T), on the matrix cores or the vector ALU
-    constexpr bool MF = use_mfma<N1, EO, T>();
-    MfmaCoef<MF ? N1 : 2> kD, kT;
-    if constexpr (MF) {
-        mfma_coef_init<N1, false>(bs, (int)(threadIdx.x & 63), kD);
-        mfma_coef_init<N1, true>(bs, (int)(threadIdx.x & 63), kT);
-    }
+    // the D-contractions: forward (D) and transposed (D^T), with
+    // row-broadcast coefficients (FP64, the orders whose tables overflow the scalar registers)
+    constexpr bool DPP = use_dpp<N1, GEO, EO, ONE, T>();
+    DppCoef<DPP ? N1 : 2> kc;
+    if constexpr (DPP) dpp_coef_init<N1>(*cs.k, (int)(threadIdx.x & 63), kc);
     auto fwd = [&](const T* in, T* out) {
-        if constexpr (MF)
-            contract_mfma<N1>(kD, in, out);
+        if constexpr (DPP)
+            contract_dpp<N1, false>(kc, bs, in, out);
         else
             contract<N1, false, EO>(cs, in, out);
     };
     auto bwd = [&](const T* in, T* out) {
-        if constexpr (MF)
-            contract_mfma<N1>(kT, in, out);
+        if constexpr (DPP)
+            contract_dpp<N1, true>(kc, bs, in, out);
         else
             contract<N1, true, EO>(cs, in, out);
     };
@@ -286,7 +329,8 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     // element groups.  The next item's X (and vertices) are fetched into registers while the
     // current one is computed and staged into LDS at the end of the current item, so HBM latency
     // overlaps with a whole item of contraction work.  Addresses are a group-uniform base plus a
-    // 32-bit lane offset; a group past the end is clamped to group 0 and slots past the last
+    // 32-bit lane offset; a group past the end is clamped to group 0 and its X reads as 0 without an
+    // access (a work-group's last prefetch), and slots past the last
     // element read the group's first element (results of such slots are never stored).
     auto clamp_group = [&](int64_t ebq) -> int64_t { return ebq < nblk ? ebq : 0; };
     auto slot_active = [&](int64_t g) -> bool {
@@ -313,8 +357,9 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
                 xc = X + (int64_t)cq * ldg;
             }
             int32_t gi[N1];
-#pragma unroll
-            for (int k = 0; k < N1; ++k) gi[k] = *at_bytes(mb, lo / sizeof(T) * 4 + k * NT * 4);
+            const uint32_t li = lo / sizeof(T) * 4;
+            const Buf bm(mb, ebq < nblk);
+            each_node<N1>([&](auto k) { gi[k] = bm.template load<k * NT * 4, int32_t>(li); });
 #pragma unroll
             for (int k = 0; k < N1; ++k) dst[k] = xc[gi[k]];
         } else {
@@ -323,8 +368,8 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
                 src = wl.template xsrc<T>(g, cq);
             else
                 src = X + (int64_t)cq * ccs + g * EPB * es;
-#pragma unroll
-            for (int k = 0; k < N1; ++k) dst[k] = *at_bytes(src, lo + k * NT * (uint32_t)sizeof(T));
+            const Buf bx(src, ebq < nblk);
+            each_node<N1>([&](auto k) { dst[k] = bx.template load<k * NT * (int)sizeof(T), T>(lo); });
         }
     };
     auto load_v = [&](int64_t ebq, double* dst) {
@@ -341,20 +386,45 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
             }
 #pragma unroll
             for (int q = 0; q < VPT; ++q) {
+                // word idx of the table below: element idx / 24, coordinate, vertex
+                const int idx = tid + q * BLOCK, el = idx / 24, r24 = idx - 24 * el;
+                const int word = el * 24 + (r24 & 7) * 3 + (r24 >> 3);
+                dst[q] = *at_bytes(src, (uint32_t)((idx < EPB * 24 && word < lim ? word : 0) * 8));
+            }
+        } else if constexpr (GEO == GEO_PARA) {
+            const int64_t g = clamp_group(ebq);
+            const double* src = geo + g * EPB * 6;
+            const int64_t lim = (E - g * EPB) * 6;
+#pragma unroll
+            for (int q = 0; q < VPT; ++q) {
                 const int idx = tid + q * BLOCK;
-                dst[q] = *at_bytes(src, (uint32_t)((idx < EPB * 24 && idx < lim ? idx : 0) * 8));
+                dst[q] = *at_bytes(src, (uint32_t)((idx < EPB * 6 && idx < lim ? idx : 0) * 8));
             }
         }
     };
     auto stage = [&](const T* x, const double* v, bool new_elem) {
+        if (inslot) {
 #pragma unroll
-        for (int k = 0; k < N1; ++k) A[S::pos(i, j, k)] = x[k];
+            for (int k = 0; k < N1; ++k) A[S::pos(i, j, k)] = x[k];
+        }
         if constexpr (is_trilinear(GEO)) {
             if (new_elem) {
 #pragma unroll
                 for (int q = 0; q < VPT; ++q) {
                     const int idx = tid + q * BLOCK;
-                    if (idx < EPB * 24) svert[idx] = v[q];
+                    // (a wave without vertex words skips the transform as a whole)
+                    if ((int)__builtin_amdgcn_readfirstlane(idx) < EPB * 24) {
+                        const double m = vertex_monomial(v[q], tid);
+                        if (idx < EPB * 24) svert[idx] = m;
+                    }
+                }
+            }
+        } else if constexpr (GEO == GEO_PARA) {
+            if (new_elem) {
+#pragma unroll
+                for (int q = 0; q < VPT; ++q) {
+                    const int idx = tid + q * BLOCK;
+                    if (idx < EPB * 6) svert[idx] = v[q];
                 }
             }
         }
@@ -377,50 +447,26 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     load_v(eb, vr);
     stage(xr, vr, true);
 
-    // where the trilinear prelude runs: at the item start (before the prefetch registers are
-    // live) or between the forward r/s contractions and the pointwise stage
-    constexpr bool EARLY = AX_EARLY_PRELUDE;
+    constexpr bool LATE = late_prefetch<N1, GEO>();
     TriCoefT<T> tc;
-    double h[6];
     while (eb < nblk) {
         const bool active = slot_active(eb);
-        const int64_t e = eb * EPB + slot;
-        const bool last_col = (c + 1 == nrhs);
+        const bool last_col = ONE || (c + 1 == nrhs);
         int64_t eb_n;
         if constexpr (W::kSlice)
             eb_n = last_col ? eb + wl.stride : eb;
         else
             eb_n = last_col ? eb + gridDim.x : eb;
         const int c_n = last_col ? 0 : c + 1;
-        if constexpr (GEO == GEO_PARA) {
-            if (c == 0) {
-                const double* he = geo + (active ? e : 0) * 6;
-                const double wij = sxw[2 * i + 1] * sxw[2 * j + 1];
-#pragma unroll
-                for (int q = 0; q < 6; ++q) h[q] = he[q] * wij;
-            }
-        }
-        // P0: (per-element geometry invariants of the home column from the staged vertices, at
-        // the point of the item where the fewest registers are live,) t-contraction in
-        // registers, then the next item's loads
-        if constexpr (EARLY) {
-            group_sync<BLOCK>();
-            if constexpr (is_trilinear(GEO)) {
-                if (c == 0) {
-                    const double* sv = svert + (slot < EPB ? slot : 0) * 24;
-                    TriCoef t64;
-                    tri_prelude([&](int v, int q) { return sv[v * 3 + q]; }, sxw[2 * i], sxw[2 * j],
-                                sxw[2 * i + 1], sxw[2 * j + 1], t64);
-                    tri_narrow(t64, tc);
-                }
-            }
-        }
+        // P0: t-contraction in registers
         T x2[N1];
         fwd(xr, x2);  // x2 = D_t x
         T xn[N1];
-        load_x(eb_n, c_n, xn);
-        if (last_col) load_v(eb_n, vr);
-        if constexpr (!EARLY) group_sync<BLOCK>();
+        if constexpr (!LATE) {
+            load_x(eb_n, c_n, xn);
+            if (last_col) load_v(eb_n, vr);
+        }
+        group_sync<BLOCK>();
         // P1: r-pencils (j,k) -> x0 in B; s-pencils (i,k) -> x1 held in registers
         T o1[N1];
         {
@@ -432,11 +478,11 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
 #pragma unroll
                 for (int n = 0; n < N1; ++n) q[n] = A[S::pos(pa, n, pb)];
                 fwd(p, o);
-                rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<S>(B, ra, rb, o);
                 fwd(q, o1);
             } else {
                 fwd(p, o);
-                rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<S>(B, ra, rb, o);
 #pragma unroll
                 for (int n = 0; n < N1; ++n) p[n] = A[S::pos(pa, n, pb)];
                 fwd(p, o1);
@@ -444,89 +490,113 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         }
         group_sync<BLOCK>();
         // P2: x1 -> A; (per-element geometry invariants of the home column from the staged vertices)
+        if (inslot) {
 #pragma unroll
-        for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
-        if constexpr (is_trilinear(GEO) && !EARLY) {
-            if (c == 0) {
-                const double* sv = svert + (slot < EPB ? slot : 0) * 24;
+            for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
+        }
+        if constexpr (is_trilinear(GEO)) {
+            if (ONE || c == 0) {
+                const double* sv = svert + (inslot ? slot : 0) * 24;
                 TriCoef t64;
-                tri_prelude([&](int v, int q) { return sv[v * 3 + q]; }, sxw[2 * i], sxw[2 * j], sxw[2 * i + 1],
-                            sxw[2 * j + 1], t64);
+                tri_prelude_monomial([&](int m, int q) { return sv[q * 8 + m]; }, sxw[2 * i], sxw[2 * j],
+                                     sxw[2 * i + 1], sxw[2 * j + 1], t64);
                 tri_narrow(t64, tc);
             }
         }
         group_sync<BLOCK>();
-        // P3: pointwise factors at the home column; r -> B, s -> A, t stays in registers
-        T tt[N1];
+        // P3: pointwise factors at the home column; r -> B, s -> A, t replaces x2 in registers
+        // (the idle lanes skip the stage: their column of x2 goes on as it is and is never stored)
         T ei = T(0);  // GATHER 2: this item's energy at the home column
+        double h[GEO == GEO_PARA ? 6 : 1];
+        if constexpr (GEO == GEO_PARA) {
+            const double* sh = svert + (inslot ? slot : 0) * 6;
+            const double wij = sxw[2 * i + 1] * sxw[2 * j + 1];
 #pragma unroll
-        for (int k = 0; k < N1; ++k) {
-            const int l = S::pos(i, j, k);
-            T x0 = B[l], x1 = A[l], xx2 = x2[k];
-            T g[6];
-            T lam_out = T(1);  // GATHER 2: lambda applied to the outputs, after the energy
-            if constexpr (GEO == GEO_TRI) {
-                T lam;
-                T tk, wk;
-                node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
-                tri_adj<T>(tc, tk, wk, g, lam);
-                if constexpr (GATHER == 2) {
-                    lam_out = lam;
-                } else {
+            for (int q = 0; q < 6; ++q) h[q] = sh[q] * wij;
+        }
+        // fields read per node: stored factors, or the scale(s) of the partial and Helmholtz forms
+        // (lanes past the last element read the group's first one)
+        constexpr int GF = GEO == GEO_STORED ? 6 : GEO == GEO_HELM ? 2 : 1;
+        const Buf bg(GEO == GEO_STORED || GEO == GEO_TRIL || GEO == GEO_HELM ? Gs + eb * (EPB * GF * NP) : nullptr);
+        const uint32_t go = (uint32_t)(((active ? slot : 0) * GF * NP + i + j * N1) * (int)sizeof(T));
+        if (inslot) {
+            each_node<N1>([&](auto k) {
+                const int l = S::pos(i, j, k);
+                T x0 = B[l], x1 = A[l], xx2 = x2[k];
+                T g[6];
+                T lam_out = T(1);  // GATHER 2: lambda applied to the outputs, after the energy
+                if constexpr (GEO == GEO_TRI) {
+                    T lam;
+                    T tk, wk;
+                    node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
+                    tri_adj<T>(tc, tk, wk, g, lam);
+                    if constexpr (GATHER == 2) {
+                        lam_out = lam;
+                    } else {
+                        x0 *= lam;
+                        x1 *= lam;
+                        xx2 *= lam;
+                    }
+                } else if constexpr (GEO == GEO_TRIL || GEO == GEO_HELM) {
+                    T tk, wk;
+                    node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
+                    const T lam = bg.template load<k * NT * (int)sizeof(T), T>(go);
+                    tri_adj_k<T>(tc, tk, g);
                     x0 *= lam;
                     x1 *= lam;
                     xx2 *= lam;
-                }
-            } else if constexpr (GEO == GEO_TRIL || GEO == GEO_HELM) {
-                T tk, wk;
-                node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
-                constexpr int LS = GEO == GEO_HELM ? 2 : 1;  // fields per element in Gs
-                const T lam = Gs[(active ? e : 0) * LS * NP + i + j * N1 + k * NT];
-                tri_adj_k<T>(tc, tk, g);
-                x0 *= lam;
-                x1 *= lam;
-                xx2 *= lam;
-            } else if constexpr (GEO == GEO_PARA) {
-                T tk, wk;
-                node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
+                } else if constexpr (GEO == GEO_PARA) {
+                    T tk, wk;
+                    node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
 #pragma unroll
-                for (int q = 0; q < 6; ++q) g[q] = T(h[q]) * wk;
-            } else {
-                const T* ge = Gs + (active ? e : 0) * 6 * NP + i + j * N1 + k * NT;
-#pragma unroll
-                for (int q = 0; q < 6; ++q) g[q] = active ? ge[q * NP] : T(0);
-            }
-            if constexpr (GATHER == 2) {
-                T bo = fma(g[0], x0, fma(g[1], x1, g[2] * xx2));
-                T ao = fma(g[1], x0, fma(g[3], x1, g[4] * xx2));
-                T to = fma(g[2], x0, fma(g[4], x1, g[5] * xx2));
-                // the node's energy (D X)^T G (D X) with G = lambda g, then G (D X) itself
-                if (active) ei += lam_out * fma(x0, bo, fma(x1, ao, xx2 * to));
-                if constexpr (GEO == GEO_TRI) {
-                    bo *= lam_out;
-                    ao *= lam_out;
-                    to *= lam_out;
+                    for (int q = 0; q < 6; ++q) g[q] = T(h[q]) * wk;
+                } else {
+                    each_node<6>([&](auto q) {
+                        g[q] = bg.template load<(q * NP + k * NT) * (int)sizeof(T), T>(go);
+                    });
                 }
-                B[l] = bo;
-                A[l] = ao;
-                tt[k] = to;
-            } else {
-                B[l] = fma(g[0], x0, fma(g[1], x1, g[2] * xx2));
-                A[l] = fma(g[1], x0, fma(g[3], x1, g[4] * xx2));
-                tt[k] = fma(g[2], x0, fma(g[4], x1, g[5] * xx2));
-            }
+                if constexpr (GATHER == 2) {
+                    T bo = fma(g[0], x0, fma(g[1], x1, g[2] * xx2));
+                    T ao = fma(g[1], x0, fma(g[3], x1, g[4] * xx2));
+                    T to = fma(g[2], x0, fma(g[4], x1, g[5] * xx2));
+                    // the node's energy (D X)^T G (D X) with G = lambda g, then G (D X) itself
+                    if (active) ei += lam_out * fma(x0, bo, fma(x1, ao, xx2 * to));
+                    if constexpr (GEO == GEO_TRI) {
+                        bo *= lam_out;
+                        ao *= lam_out;
+                        to *= lam_out;
+                    }
+                    B[l] = bo;
+                    A[l] = ao;
+                    x2[k] = to;
+                } else {
+                    const T bo = fma(g[0], x0, fma(g[1], x1, g[2] * xx2));
+                    const T ao = fma(g[1], x0, fma(g[3], x1, g[4] * xx2));
+                    B[l] = bo;
+                    A[l] = ao;
+                    x2[k] = fma(g[2], x0, fma(g[4], x1, g[5] * xx2));
+                }
+            });
         }
         if constexpr (GATHER == 2) sen[tid] += (double)ei;
-        T y2[N1];
-        bwd(tt, y2);  // D_t^T t
-        // Helmholtz: Lambda3 and this item's X at the home column for the mass term, loaded here
-        // (X again, now from the cache) so that they are in flight during the next phase
+        // Helmholtz: Lambda3 and this item's X at the home column for the mass term (X again, now
+        // from the cache), in flight during the t-contraction
         T l3v[GEO == GEO_HELM ? N1 : 1], xv[GEO == GEO_HELM ? N1 : 1];
         if constexpr (GEO == GEO_HELM) {
-            const T* l3 = Gs + ((active ? e : 0) * 2 + 1) * NP + i + j * N1;
-#pragma unroll
-            for (int k = 0; k < N1; ++k) l3v[k] = l3[k * NT];
+            each_node<N1>([&](auto k) { l3v[k] = bg.template load<(NP + k * NT) * (int)sizeof(T), T>(go); });
             load_x(eb, c, xv);
+        }
+        T y2[N1];
+        bwd(x2, y2);  // D_t^T t
+        if constexpr (GEO == GEO_HELM) {
+#pragma unroll
+            for (int k = 0; k < N1; ++k) y2[k] = fma(l3v[k], xv[k], y2[k]);
+            // (the next item's loads stay behind the mass term, whose operands are dead by then)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (LATE) {
+            load_x(eb_n, c_n, xn);
+            if (last_col) load_v(eb_n, vr);
         }
         group_sync<BLOCK>();
         // P4: D_r^T r in place on the r-pencils; D_s^T s into registers
@@ -538,53 +608,36 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
 #pragma unroll
                 for (int n = 0; n < N1; ++n) q[n] = A[S::pos(pa, n, pb)];
                 bwd(p, o);
-                rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<S>(B, ra, rb, o);
                 bwd(q, o1);
             } else {
                 bwd(p, o);
-                rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<S>(B, ra, rb, o);
 #pragma unroll
                 for (int n = 0; n < N1; ++n) p[n] = A[S::pos(pa, n, pb)];
                 bwd(p, o1);
             }
-#if AX_MERGE_RS
             // each s-pencil is read and written by its own lane only
+            if (inslot) {
 #pragma unroll
-            for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
-#endif
+                for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
+            }
         }
         group_sync<BLOCK>();
-        if constexpr (GEO == GEO_HELM) {
-#pragma unroll
-            for (int k = 0; k < N1; ++k) y2[k] = fma(l3v[k], xv[k], y2[k]);
-        }
         T* yb;
         if constexpr (W::kList)
             yb = wl.template ydst<T>(eb, c);
         else
             yb = Y + (int64_t)c * ccs + eb * EPB * es;
         const uint32_t lo = home_off(true);
-#if AX_MERGE_RS
         // P5: Y = (D_r^T r + D_s^T s) + D_t^T t
         if (active) {
-#pragma unroll
-            for (int k = 0; k < N1; ++k) {
+            const Buf by(yb);
+            each_node<N1>([&](auto k) {
                 const int l = S::pos(i, j, k);
-                *at_bytes(yb, lo + k * NT * (uint32_t)sizeof(T)) = (B[l] + A[l]) + y2[k];
-            }
+                by.template store<k * NT * (int)sizeof(T), T>(lo, (B[l] + A[l]) + y2[k]);
+            });
         }
-#else
-        // P5: add D_s^T s on the s-pencils
-#pragma unroll
-        for (int a = 0; a < N1; ++a) B[S::pos(pa, a, pb)] += o1[a];
-        group_sync<BLOCK>();
-        // P6: Y = (D_r^T r + D_s^T s) + D_t^T t
-        if (active) {
-#pragma unroll
-            for (int k = 0; k < N1; ++k)
-                *at_bytes(yb, lo + k * NT * (uint32_t)sizeof(T)) = B[S::pos(i, j, k)] + y2[k];
-        }
-#endif
         // stage the next item: this lane's own home positions (read above by this lane only)
         // and the vertex table (last read before the barriers of P3 and P4)
         stage(xn, vr, last_col);
@@ -620,46 +673,41 @@ constexpr int min_waves()
     return tile_waves(N1, GEO, sizeof(T) == 4);
 }
 
-// Entry points: the tables of orders that fit the scalar register file stay resident; the
-// others are reloaded per output row through the kernel-argument segment (one struct argument).
-template <int N1, int GEO, bool EO, int GATHER, int EPBX, typename T>
+// ONE: a single column (nrhs = 1), so that the per-column factor coefficients die with the
+// pointwise stage instead of living through the item for the next column.
+template <int N1, int GEO, bool EO, int GATHER, int EPBX, bool ONE, typename T>
 __global__ void __launch_bounds__((Tile<N1, EPBX>::BLOCK), (min_waves<N1, GEO, T>()))
-ax_local_kernel(int64_t E, int nrhs, const double* __restrict__ geo, const T* __restrict__ Gs,
-                const T* __restrict__ X, T* __restrict__ Y, const Basis<T> bs,
-                const int32_t* __restrict__ l2g, int64_t ldg, int64_t es, int64_t ccs, double* __restrict__ epart)
+ax_local_kernel(const AxArgs<T> ka)
 {
-    ax_local_body<N1, GEO, EO, GATHER, EPBX, T>(E, nrhs, geo, Gs, X, Y, bs, l2g, ldg, es, ccs, epart,
-                                                CoefResident<T>{bs});
-}
-
-template <int N1, int GEO, bool EO, int GATHER, int EPBX, typename T>
-__global__ void __launch_bounds__((Tile<N1, EPBX>::BLOCK), (min_waves<N1, GEO, T>()))
-ax_local_kernel_rl(const AxArgs<T> ka)
-{
-    const CoefReload<T> cs = karg_coefs<T, AxArgs<T>>();
-    ax_local_body<N1, GEO, EO, GATHER, EPBX, T>(ka.E, ka.nrhs, ka.geo, ka.Gs, ka.X, ka.Y, ka.bs, ka.l2g, ka.ldg, ka.es,
-                                                ka.ccs, ka.epart, cs);
+    if constexpr (reload_coefs<N1, EO, T>() || use_dpp<N1, GEO, EO, ONE, T>())
+        ax_local_body<N1, GEO, EO, GATHER, EPBX, ONE, T>(ka.E, ka.nrhs, ka.geo, ka.Gs, ka.X, ka.Y, ka.bs, ka.l2g,
+                                                         ka.ldg, ka.es, ka.ccs, ka.epart, karg_coefs<T, AxArgs<T>>());
+    else
+        ax_local_body<N1, GEO, EO, GATHER, EPBX, ONE, T>(ka.E, ka.nrhs, ka.geo, ka.Gs, ka.X, ka.Y, ka.bs, ka.l2g,
+                                                         ka.ldg, ka.es, ka.ccs, ka.epart, CoefResident<T>{ka.bs});
 }
 
 // fo (GATHER 2 only): the energy partials; fo->nparts gets the grid size.
-template <int N1, int GEO, bool EO, int GATHER, int EPBX, typename T>
+template <int N1, int GEO, bool EO, int GATHER, int EPBX, typename T, bool ONE = GATHER == 2>
 static int launch_tile(int64_t E, int nrhs, const double* geo, const T* Gs, const T* X, T* Y, const Basis<T>& bs,
                        int grid_mult, hipStream_t st, const int32_t* l2g, int64_t ldg, int64_t es, int64_t ccs,
                        FusedOut* fo = nullptr)
 {
+    if constexpr (!ONE && is_trilinear(GEO))
+        if (nrhs == 1)
+            return launch_tile<N1, GEO, EO, GATHER, EPBX, T, true>(E, nrhs, geo, Gs, X, Y, bs, grid_mult, st, l2g, ldg,
+                                                                   es, ccs, fo);
     using TL = Tile<N1, EPBX>;
+    const auto kernel = &ax_local_kernel<N1, GEO, EO, GATHER, EPBX, ONE, T>;
     static int per = 0;  // resident work-groups per CU for this instantiation
     static int cus = 0;
     if (per == 0) {
         int dev = 0, c = 256, q = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
-        const void* kf;
-        if constexpr (reload_coefs<N1, GEO, T>())
-            kf = reinterpret_cast<const void*>(ax_local_kernel_rl<N1, GEO, EO, GATHER, EPBX, T>);
-        else
-            kf = reinterpret_cast<const void*>(ax_local_kernel<N1, GEO, EO, GATHER, EPBX, T>);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, kf, TL::BLOCK, 0) != hipSuccess || q < 1)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, reinterpret_cast<const void*>(kernel), TL::BLOCK, 0) !=
+                hipSuccess ||
+            q < 1)
             q = 1;
         cus = c;
         per = q;
@@ -678,14 +726,8 @@ static int launch_tile(int64_t E, int nrhs, const double* geo, const T* Gs, cons
         epart = fo->epart;
         fo->nparts = blocks;
     }
-    if constexpr (reload_coefs<N1, GEO, T>()) {
-        const AxArgs<T> ka{E, nrhs, geo, Gs, X, Y, l2g, ldg, es, ccs, epart, bs};
-        hipLaunchKernelGGL((ax_local_kernel_rl<N1, GEO, EO, GATHER, EPBX, T>), dim3((unsigned)blocks),
-                           dim3(TL::BLOCK), 0, st, ka);
-    } else {
-        hipLaunchKernelGGL((ax_local_kernel<N1, GEO, EO, GATHER, EPBX, T>), dim3((unsigned)blocks), dim3(TL::BLOCK),
-                           0, st, E, nrhs, geo, Gs, X, Y, bs, l2g, ldg, es, ccs, epart);
-    }
+    const AxArgs<T> ka{E, nrhs, geo, Gs, X, Y, l2g, ldg, es, ccs, epart, bs};
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TL::BLOCK), 0, st, ka);
     return hip_check(hipGetLastError(), "ax_local launch");
 }
 
@@ -737,13 +779,13 @@ static int launch_n1(int64_t E, int nrhs, const double* geo, const T* Gs, const 
         }
     }
     if (!eo)
-        return launch_tile<N1, GEO, false, false, S::EPB, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st, nullptr, 0, es, ccs);
+        return launch_tile<N1, GEO, false, 0, S::EPB, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st, nullptr, 0, es, ccs);
     if constexpr (S::EPB_ALT != S::EPB) {
         if (tu.tile_alt)
-            return launch_tile<N1, GEO, true, false, S::EPB_ALT, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st,
+            return launch_tile<N1, GEO, true, 0, S::EPB_ALT, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st,
                                                                     nullptr, 0, es, ccs);
     }
-    return launch_tile<N1, GEO, true, false, S::EPB, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st, nullptr, 0, es, ccs);
+    return launch_tile<N1, GEO, true, 0, S::EPB, T>(E, nrhs, geo, Gs, X, Y, bs, tu.grid_mult, st, nullptr, 0, es, ccs);
 }
 
 template <int GEO, typename T>
@@ -755,11 +797,16 @@ static int dispatch(int N, int64_t E, int nrhs, const double* geo, const T* Gs, 
     switch (N + 1) {
 #define AX_CASE(n1) \
     case n1: return launch_n1<n1, GEO, T>(E, nrhs, geo, Gs, X, Y, D, xi, w, st, l2g, ldg, es, ccs, fo);
+#ifdef AX_FEW
+        AX_CASE(3) AX_CASE(4) AX_CASE(6) AX_CASE(7) AX_CASE(8) AX_CASE(9) AX_CASE(10) AX_CASE(12) AX_CASE(13) AX_CASE(16)
+    default: return fail(AX_ERR_UNSUPPORTED, "few");
+#else
         AX_CASE(2) AX_CASE(3) AX_CASE(4) AX_CASE(5) AX_CASE(6) AX_CASE(7) AX_CASE(8) AX_CASE(9)
         AX_CASE(10) AX_CASE(11) AX_CASE(12) AX_CASE(13) AX_CASE(14) AX_CASE(15) AX_CASE(16)
 #undef AX_CASE
     default:
         return fail(AX_ERR_UNSUPPORTED, "order N=%d outside [1,15]", N);
+#endif
     }
 }
 }  // namespace ax

@@ -121,7 +121,7 @@ order_tile_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ mes
     static_assert(batched_tile_available(N1, sizeof(T) == 4), "no batched tile kernel at this order");
     const MeshListWalk<EPB, NP> wl{items, meshes, n};
     const Basis<T>& bs = *bsp;
-    ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, T>(0, nrhs, nullptr, nullptr, nullptr, nullptr, bs, nullptr, 0,
+    ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, false, T>(0, nrhs, nullptr, nullptr, nullptr, nullptr, bs, nullptr, 0,
                                                          NP, 0, nullptr, CoefConst<T>{as_constant(bsp)}, wl);
 }
 
@@ -147,7 +147,7 @@ order_slice_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ me
     const BMesh m = meshes[sl.mesh];
     const MeshSliceWalk wl{sl.eb, m.wgs};
     const Basis<T>& bs = *bsp;
-    ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, T>(m.E, nrhs, m.verts, nullptr, static_cast<const T*>(m.X),
+    ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, false, T>(m.E, nrhs, m.verts, nullptr, static_cast<const T*>(m.X),
                                                          static_cast<T*>(m.Y), bs, G ? m.l2g : nullptr, m.ldg, NP, m.ld,
                                                          nullptr, CoefConst<T>{as_constant(bsp)}, wl);
 }

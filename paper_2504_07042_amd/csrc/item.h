@@ -75,9 +75,16 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
     const T* X = reinterpret_cast<const T*>(m.X);
     T* Y = reinterpret_cast<T*>(m.Y);
 
-    for (int q = tid; q < EPB * 24; q += S::BLOCK) {
-        const int64_t off = eb * EPB * 24 + q;
-        svert[q] = off < m.E * 24 ? m.verts[off] : 0.0;
+    // the monomial coefficients of each element's map, [element][coordinate][monomial]
+#pragma unroll
+    for (int g = 0; g < (EPB * 24 + S::BLOCK - 1) / S::BLOCK; ++g) {
+        const int q = tid + g * S::BLOCK;
+        if ((int)__builtin_amdgcn_readfirstlane(q) < EPB * 24) {
+            const int el = q / 24, r24 = q - 24 * el;
+            const int64_t off = (eb * EPB + el) * 24 + (r24 & 7) * 3 + (r24 >> 3);
+            const double mono = vertex_monomial(q < EPB * 24 && off < m.E * 24 ? m.verts[off] : 0.0, tid);
+            if (q < EPB * 24) svert[q] = mono;
+        }
     }
     lds_barrier();
     TriCoefT<T> tc;
@@ -85,7 +92,7 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         const double* sv = svert + slot * 24;
         const C b = cs.row();
         TriCoef t64;
-        tri_prelude([&](int v, int q) { return sv[v * 3 + q]; }, b.xi(i), b.xi(j), b.w(i), b.w(j), t64);
+        tri_prelude_monomial([&](int mo, int q) { return sv[q * 8 + mo]; }, b.xi(i), b.xi(j), b.w(i), b.w(j), t64);
         tri_narrow(t64, tc);
     }
     for (int c = 0; c < nrhs; ++c) {
