@@ -66,30 +66,16 @@ constexpr int item_waves(int N1, bool fp32, bool partial, int alt)
     return alt ? (d == 2 ? 3 : 4) : d;
 }
 
-// Which kernel runs when the tuning table says "auto" (measured on gfx950, interleaved runs).
-// FP64 full form: the per-item kernel for N1 = 6, 7 and 9..15 (faster than the prefetching
-// kernel there, about even at N1 = 5, slower at N1 <= 4, 8 and 16).  FP64 partial form: the
-// per-item kernel from N1 = 9 (the prefetching kernel, with fewer live registers in this form,
-// was faster at N1 = 6).  FP32 full form: the per-item kernel from N1 = 9 (at five waves per SIMD:
-// +7-8 % at N1 = 9 and 10, +13-15 % at N1 = 12, 15, where the prefetching kernel runs at two).
-// FP32 partial form: from N1 = 13 (+18 % at 13, +7 % at 14, +2 % at 15; even at 10 and 8-10 %
-// behind at 11, 12).
-#ifndef AX_ITEM_LO
-#define AX_ITEM_LO 6
-#endif
-#ifndef AX_ITEM_LO_F32
-#define AX_ITEM_LO_F32 9
-#endif
-#ifndef AX_ITEM_PL_LO_F32
-#define AX_ITEM_PL_LO_F32 13
-#endif
+// Which kernel runs when the tuning table says "auto" (measured on gfx950, GDOF/s at 2^24 nodes,
+// tile against per-item kernel).  FP64: the tile kernel (N1 = 5: 199 against 191; 6: 203, 194;
+// 9: 204, 171; 10: 174, 151; 13: 163, 142) except the full form at N1 = 7, where the two tie (205,
+// 200).  FP32: the per-item kernel at N1 = 13 (212, 257; partial form 215, 264) and, in the full
+// form, 9 (299, 306), 14 (195, 210) and 15 (199, 205); the tile kernel elsewhere (10: 290, 259; 12: 265,
+// 220).
 constexpr bool item_default(int N1, int geo, bool fp32)
 {
-    if (N1 > 15) return false;
-    if (fp32)
-        return (geo == GEO_TRI && N1 >= AX_ITEM_LO_F32 && N1 >= 9) ||
-               (geo == GEO_TRIL && N1 >= AX_ITEM_PL_LO_F32 && N1 >= 13);
-    return (geo == GEO_TRI && N1 >= AX_ITEM_LO && N1 != 8) || (geo == GEO_TRIL && N1 >= 9);
+    if (geo == GEO_TRI) return fp32 ? N1 == 9 || (N1 >= 13 && N1 <= 15) : N1 == 7;
+    return geo == GEO_TRIL && fp32 && N1 == 13;
 }
 
 // Orders with a batched tile kernel (the single-mesh tile body walking the batch's work list):
@@ -112,58 +98,10 @@ constexpr bool item_available(int N1, int geo)
     return (geo == GEO_TRI && N1 >= 2 && N1 <= 16) || (geo == GEO_TRIL && N1 >= 9 && N1 <= 16);
 }
 
-// XOR-swizzled LDS layout for N1 = 8 (no padding; conflict-free for the home, r-pencil and
-// s-pencil access patterns) instead of the padded row stride.
-#ifndef AX_LDS_SWIZZLE
-#define AX_LDS_SWIZZLE 0
-#endif
-// LDS layout for N1 = 8: 0 = word i + 9 j + 72 k (row stride padded to 9); 1 = word
-// i + 8 j + 65 k with the r-pencils assigned to lanes k-fastest; 2 (8-byte words only) = word
-// i + 8 j + 66 k, r-pencils k-fastest and moved as 16-byte accesses, s-pencils assigned so that
-// each group of 16 lanes takes the slices k and k + 4 (4-byte words: i + 8 j + 68 k, each group
-// of 32 lanes takes the slices k = 0, 2, 4, 6 or 1, 3, 5, 7, so i + 4 k covers the 32 banks; a
-// 16-byte r-pencil access starts at bank 8 j + 4 k, 8 lanes k = 0..7 cover them).  With 64-bit
-// accesses served 16 lanes per
-// clock over 32 four-byte banks, layout 0 is conflict-free for the r- and s-pencils and 2-way
-// conflicted for the home columns; layout 1 is conflict-free for the home columns and the
-// r-pencils and 2-way conflicted for the s-pencils (no additive layout is conflict-free for all
-// three patterns with lanes taking pencils in order); layout 2 is conflict-free for all three:
-// home columns i + 8 j (two rows j per 16 lanes) cover the 16 double-word banks, each 16-byte
-// r-pencil access starts at bank 2 k (8 lanes k = 0..7 cover the 16 banks), and s-pencil lanes
-// i + 2 k with k and k + 4 cover them too.
-#ifndef AX_LDS_LAYOUT
-#define AX_LDS_LAYOUT 2
-#endif
-
-// Element shape of order N1 - 1 and its LDS layout; WB = bytes per stored value.
-template <int N1, int WB = 8>
+// Element shape of order N1 - 1.
+template <int N1>
 struct Shape {
-    static constexpr int NN = N1;                             // points per direction
     static constexpr int NT = N1 * N1;                        // lanes per element
-    static constexpr bool SWZ = AX_LDS_SWIZZLE && N1 == 8;
-    static constexpr bool L2 = !SWZ && AX_LDS_LAYOUT == 2 && N1 == 8 && (WB == 8 || WB == 4);
-    static constexpr bool L1 = !SWZ && AX_LDS_LAYOUT == 1 && N1 == 8;
-    static constexpr int SJ = (L1 || L2) ? 8 : (N1 % 2 == 0) ? N1 + 1 : N1;   // LDS row stride
-    static constexpr int SK = L2 ? (WB == 8 ? 66 : 68) : L1 ? 65 : N1 * SJ;    // LDS slice stride
-    static constexpr int FS = SWZ ? 512 : (L1 || L2) ? 8 * SK : N1 * SK;       // LDS words per field
-    // LDS word of node (i, j, k) within one field
-    __device__ static __forceinline__ int pos(int i, int j, int k)
-    {
-        if constexpr (SWZ)
-            return 64 * k + 8 * (j ^ (k & 1)) + (i ^ ((j >> 1) << 1));
-        else
-            return k * SK + j * SJ + i;
-    }
-    // pencil lanes: the r-pencil (j, k) and the s-pencil (i, k) a lane owns
-    __device__ static __forceinline__ int rpa(int lane) { return (L1 || L2) ? lane / N1 : lane % N1; }
-    __device__ static __forceinline__ int rpb(int lane) { return (L1 || L2) ? lane % N1 : lane / N1; }
-    __device__ static __forceinline__ int spa(int lane) { return lane % N1; }
-    __device__ static __forceinline__ int spb(int lane)
-    {
-        if constexpr (L2 && WB == 8) return ((lane >> 3) & 1) * 4 + (lane >> 4);
-        if constexpr (L2 && WB == 4) return 2 * ((lane >> 3) & 3) + (lane >> 5);
-        return lane / N1;
-    }
     static constexpr int NP = N1 * N1 * N1;                   // nodes per element
     // elements per work-group: fill (nearly) whole waves while keeping LDS modest
     static constexpr int EPB = N1 == 2 ? 16 : N1 == 3 ? 7 : N1 == 4 ? 4 : N1 == 5 ? 5
@@ -174,6 +112,130 @@ struct Shape {
                                  : N1 == 6 ? 14 : N1 == 7 ? 10 : N1 == 8 ? 2 : N1 <= 11 ? 1 : EPB;
     static constexpr int BLOCK = ((EPB * NT + 63) / 64) * 64;
 };
+
+// LDS layout of a work-group: EPB elements of order N1 - 1, two fields each of
+// WB-byte values, node (i, j, k) at word i + SJ j + SK k of a field, SJ = N1.
+//
+// The LDS serves 128 bytes per clock, G = 128 / WB lanes at a time, without a conflict when their
+// words differ modulo G.  Home columns (lane i + N1 j) are consecutive words, also across elements:
+// the element stride ST continues the sequence modulo G.  The r-pencils (j, k) and s-pencils (i, k)
+// may be owned by any lanes, so they are dealt out such that every G lanes start at words that
+// differ modulo G (make()); with a few words of padding per slice that works out almost
+// perfectly at every order: 0-7 % above the conflict-free cycles (N1 = 2, 4: 27 %) where rows
+// padded to an odd number of words with pencils in lane order cost 7-77 % (77 % at N1 = 6).
+// Measured with those the conflicts took 0.21 of the kernel at N1 = 6 and 0.19 at N1 = 10 (FP64
+// trilinear).
+// N1 = 8 (slices of 64 + 2 words, 64 + 4 in FP32) moves its r-pencils as 16-byte accesses: lanes
+// take them k-fastest, so 8 lanes k = 0..7 start at banks 4 bytes x 2 k (FP32: 8 j + 4 k) and
+// cover all; the s-pencils are assigned so that each group of 16 lanes takes the slices k and
+// k + 4 (FP32: 32 lanes, the even or the odd slices), which cover the banks too.
+constexpr int tile_slice_pad(int N1, int WB)
+{
+    constexpr int p8[17] = {0, 0, 1, 6, 3, 4, 5, 4, 2, 1, 3, 4, 3, 0, 1, 0, 1};
+    constexpr int p4[17] = {0, 0, 1, 22, 3, 4, 3, 4, 4, 3, 9, 4, 1, 0, 3, 1, 5};
+    return WB == 8 ? p8[N1] : p4[N1];
+}
+
+template <int N1, int EPB, int WB>
+struct TileLds {
+    static constexpr int NT = N1 * N1, SJ = N1, SK = NT + tile_slice_pad(N1, WB), G = 128 / WB;
+    static constexpr bool V16 = N1 == 8;  // r-pencils start on 16-byte boundaries
+    static constexpr int FS = N1 == 8 ? 8 * SK : (N1 - 1) * SK + NT;
+    static constexpr int ST = EPB == 1 || N1 == 8 ? 2 * FS : 2 * FS + ((NT - 2 * FS) % G + G) % G;
+    static constexpr int WORDS = (EPB - 1) * ST + 2 * FS;
+    static constexpr int LANES = EPB * NT;
+    static_assert(WORDS <= 0xffff, "pencil offsets are 16-bit words");
+    static __device__ __forceinline__ constexpr int pos(int i, int j, int k) { return k * SK + j * SJ + i; }
+
+    // first word of the r-pencil and of the s-pencil each lane owns
+    struct Pencils {
+        uint16_t r[LANES], s[LANES];
+    };
+    // `w`: the pencils' first words in any order; on return every G of them differ modulo G as far
+    // as possible (each group takes one pencil from every residue class, fullest classes first)
+    static constexpr void deal(uint16_t* w)
+    {
+        uint16_t c[G][LANES] = {};
+        int n[G] = {}, left = LANES;
+        for (int q = 0; q < LANES; ++q) c[w[q] % G][n[w[q] % G]++] = w[q];
+        for (int q = 0; q < LANES;) {
+            const int need = left < G ? left : G;
+            bool used[G] = {};
+            for (int t = 0; t < need; ++t) {
+                int best = -1;
+                for (int r = 0; r < G; ++r)
+                    if (!used[r] && n[r] > 0 && (best < 0 || n[r] > n[best])) best = r;
+                if (best < 0)
+                    for (int r = 0; r < G; ++r)
+                        if (n[r] > 0 && (best < 0 || n[r] > n[best])) best = r;
+                used[best] = true;
+                w[q++] = c[best][--n[best]];
+                --left;
+            }
+        }
+    }
+    static constexpr Pencils make()
+    {
+        Pencils p{};
+        for (int e = 0; e < EPB; ++e)
+            for (int l = 0; l < NT; ++l) {
+                int ra = l % N1, rb = l / N1, sa = l % N1, sb = l / N1;
+                if (N1 == 8) {
+                    ra = l / N1;
+                    rb = l % N1;
+                    sb = WB == 8 ? ((l >> 3) & 1) * 4 + (l >> 4) : 2 * ((l >> 3) & 3) + (l >> 5);
+                }
+                p.r[e * NT + l] = (uint16_t)(e * ST + ra * SJ + rb * SK);
+                p.s[e * NT + l] = (uint16_t)(e * ST + sa + sb * SK);
+            }
+        if (N1 != 8) {
+            deal(p.r);
+            deal(p.s);
+        }
+        return p;
+    }
+    static constexpr Pencils pencils = make();
+};
+
+// An r-pencil: contiguous words, moved as 16-byte accesses where the layout aligns them.
+template <typename L, int N1, typename T>
+__device__ __forceinline__ void rpencil_read(const T* F, T* p)
+{
+    if constexpr (L::V16) {
+        constexpr int W = 16 / sizeof(T);  // values per 16-byte access
+        typedef T v16 __attribute__((ext_vector_type(W)));
+        const v16* q = reinterpret_cast<const v16*>(F);
+#pragma unroll
+        for (int m = 0; m < N1 / W; ++m) {
+            const v16 v = q[m];
+#pragma unroll
+            for (int u = 0; u < W; ++u) p[W * m + u] = v[u];
+        }
+    } else {
+#pragma unroll
+        for (int n = 0; n < N1; ++n) p[n] = F[n];
+    }
+}
+
+template <typename L, int N1, typename T>
+__device__ __forceinline__ void rpencil_write(T* F, const T* o)
+{
+    if constexpr (L::V16) {
+        constexpr int W = 16 / sizeof(T);
+        typedef T v16 __attribute__((ext_vector_type(W)));
+        v16* q = reinterpret_cast<v16*>(F);
+#pragma unroll
+        for (int m = 0; m < N1 / W; ++m) {
+            v16 v;
+#pragma unroll
+            for (int u = 0; u < W; ++u) v[u] = o[W * m + u];
+            q[m] = v;
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < N1; ++a) F[a] = o[a];
+    }
+}
 
 // Waves per SIMD the register allocation of the prefetching (tile) kernel must allow: the most at
 // which a single-column kernel does not spill (a few registers at N1 = 4 and FP32 aside).  FP64:

@@ -14,8 +14,8 @@
 //     cuts LDS reads per FMA from 1 to 1/N1, which matters because a CDNA4 CU moves 16 doubles
 //     per clock out of LDS but retires 64 FP64 FMAs per clock.
 //   * The t-contractions run on the home lane's registers.  The r- and s-contractions read
-//     pencils from an LDS copy of the element (row stride padded to an odd number of words so
-//     both pencil directions are free of bank conflicts) and hand results back through LDS.
+//     pencils from an LDS copy of the element and hand results back through LDS; which lane owns
+//     which pencil follows from the LDS banks (TileLds).
 //   * The FP64 matrix cores of gfx950 run at the same rate as FP64 FMA on the vector unit and do
 //     not overlap with it, so the FP64 contractions stay on the vector unit.
 #pragma once
@@ -140,49 +140,6 @@ __device__ __forceinline__ void each_node(F&& f)
     }
 }
 
-// The r-pencil (., j, k) of a field: contiguous words i = 0..N1-1.  With layout 2 every pencil
-// starts on a 16-byte boundary and moves as 16-byte accesses (two doubles or four floats each).
-template <typename S, typename T>
-__device__ __forceinline__ void rpencil_read(const T* F, int j, int k, T* p)
-{
-    constexpr int N1 = S::NN;
-    if constexpr (S::L2) {
-        constexpr int W = 16 / sizeof(T);  // values per 16-byte access
-        typedef T v16 __attribute__((ext_vector_type(W)));
-        const v16* q = reinterpret_cast<const v16*>(F + S::pos(0, j, k));
-#pragma unroll
-        for (int m = 0; m < N1 / W; ++m) {
-            const v16 v = q[m];
-#pragma unroll
-            for (int u = 0; u < W; ++u) p[W * m + u] = v[u];
-        }
-    } else {
-#pragma unroll
-        for (int n = 0; n < N1; ++n) p[n] = F[S::pos(n, j, k)];
-    }
-}
-
-template <typename S, typename T>
-__device__ __forceinline__ void rpencil_write(T* F, int j, int k, const T* o)
-{
-    constexpr int N1 = S::NN;
-    if constexpr (S::L2) {
-        constexpr int W = 16 / sizeof(T);
-        typedef T v16 __attribute__((ext_vector_type(W)));
-        v16* q = reinterpret_cast<v16*>(F + S::pos(0, j, k));
-#pragma unroll
-        for (int m = 0; m < N1 / W; ++m) {
-            v16 v;
-#pragma unroll
-            for (int u = 0; u < W; ++u) v[u] = o[W * m + u];
-            q[m] = v;
-        }
-    } else {
-#pragma unroll
-        for (int a = 0; a < N1; ++a) F[S::pos(a, j, k)] = o[a];
-    }
-}
-
 // Synchronisation of the work-group between LDS phases.  A work-group of one wave (N1 = 8 with one
 // element per group) needs no hardware barrier and no wait for its LDS writes: the LDS performs the
 // accesses of one wave in issue order, so a later read by any lane sees an earlier write by any
@@ -266,13 +223,13 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
               const C& cs, const W& wl = W{})
 {
     static_assert(!W::kList || GEO == GEO_TRI, "work lists carry trilinear meshes");
-    using S = Shape<N1, sizeof(T)>;
     using TL = Tile<N1, EPBX>;
-    constexpr int NT = S::NT, FS = S::FS, NP = S::NP, EPB = TL::EPB;
+    using L = TileLds<N1, EPBX, sizeof(T)>;
+    constexpr int NT = L::NT, FS = L::FS, SJ = L::SJ, SK = L::SK, NP = N1 * N1 * N1, EPB = TL::EPB;
     constexpr int BLOCK = TL::BLOCK;
     constexpr int NV = is_trilinear(GEO) ? 24 : GEO == GEO_PARA ? 6 : 0;   // geometry words per element
     constexpr int VPT = (EPB * NV + BLOCK - 1) / BLOCK;          // and per thread
-    __shared__ __attribute__((aligned(16))) T smem[EPB * 2 * FS];
+    __shared__ __attribute__((aligned(16))) T smem[L::WORDS];
     // trilinear: the monomial coefficients of the map, [element][coordinate][monomial];
     // parallelepiped: h
     __shared__ __attribute__((aligned(16))) double svert[NV > 0 ? EPB * NV : 1];
@@ -291,15 +248,20 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     const int lane = tid - slot * NT;
     // lanes past the last slot read slot 0's fields and write nothing
     const bool inslot = TL::FULL || slot < EPB;
-    T* __restrict__ A = smem + (inslot ? slot : 0) * 2 * FS;
-    // the second field's base in its own register: as an offset from the first it leaves the reach
-    // of the paired LDS accesses and costs one address register per pair
-    int bo = (inslot ? slot : 0) * 2 * FS + FS;
-    asm("" : "+v"(bo));
-    T* __restrict__ B = smem + bo;
     const int i = lane % N1, j = lane / N1;    // home lane: node column (i, j, :)
-    const int pa = S::spa(lane), pb = S::spb(lane);  // s-pencil lane (i, k)
-    const int ra = S::rpa(lane), rb = S::rpb(lane);  // r-pencil lane (j, k)
+    // The fields A (X, then s) and B (r) of this lane's element at its home column, and the first
+    // words of the r- and s-pencil it owns (of any element of the group).  The second field's
+    // addresses sit in registers of their own: as offsets from the first they leave the reach of
+    // the paired LDS accesses and cost one address register per pair.
+    const int ro = L::pencils.r[inslot ? tid : 0], so = L::pencils.s[inslot ? tid : 0];
+    const int ho = (inslot ? slot : 0) * L::ST + j * SJ + i;
+    int hb = ho + FS, rb = ro + FS;
+    asm("" : "+v"(hb), "+v"(rb));
+    T* A = smem + ho;
+    T* B = smem + hb;
+    T* Ar = smem + ro;
+    T* Br = smem + rb;
+    T* As = smem + so;
     int64_t nblk;
     if constexpr (W::kList)
         nblk = wl.groups();
@@ -405,7 +367,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     auto stage = [&](const T* x, const double* v, bool new_elem) {
         if (inslot) {
 #pragma unroll
-            for (int k = 0; k < N1; ++k) A[S::pos(i, j, k)] = x[k];
+            for (int k = 0; k < N1; ++k) A[k * SK] = x[k];
         }
         if constexpr (is_trilinear(GEO)) {
             if (new_elem) {
@@ -471,20 +433,20 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         T o1[N1];
         {
             T p[N1], o[N1];
-            rpencil_read<S>(A, ra, rb, p);
+            rpencil_read<L, N1>(Ar, p);
             if constexpr ((s_hoist<N1, GEO, T>() & 1) != 0) {
                 // the s-pencil is read before the r-contraction so that its latency overlaps it
                 T q[N1];
 #pragma unroll
-                for (int n = 0; n < N1; ++n) q[n] = A[S::pos(pa, n, pb)];
+                for (int n = 0; n < N1; ++n) q[n] = As[n * SJ];
                 fwd(p, o);
-                if (inslot) rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<L, N1>(Br, o);
                 fwd(q, o1);
             } else {
                 fwd(p, o);
-                if (inslot) rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<L, N1>(Br, o);
 #pragma unroll
-                for (int n = 0; n < N1; ++n) p[n] = A[S::pos(pa, n, pb)];
+                for (int n = 0; n < N1; ++n) p[n] = As[n * SJ];
                 fwd(p, o1);
             }
         }
@@ -492,7 +454,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         // P2: x1 -> A; (per-element geometry invariants of the home column from the staged vertices)
         if (inslot) {
 #pragma unroll
-            for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
+            for (int a = 0; a < N1; ++a) As[a * SJ] = o1[a];
         }
         if constexpr (is_trilinear(GEO)) {
             if (ONE || c == 0) {
@@ -520,9 +482,16 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         const Buf bg(GEO == GEO_STORED || GEO == GEO_TRIL || GEO == GEO_HELM ? Gs + eb * (EPB * GF * NP) : nullptr);
         const uint32_t go = (uint32_t)(((active ? slot : 0) * GF * NP + i + j * N1) * (int)sizeof(T));
         if (inslot) {
+            // the next node's x0, x1 are read before this node's results are written: the compiler
+            // cannot tell the two fields' addresses apart and would keep the reads behind the writes
+            T n0 = B[0], n1 = A[0];
             each_node<N1>([&](auto k) {
-                const int l = S::pos(i, j, k);
-                T x0 = B[l], x1 = A[l], xx2 = x2[k];
+                constexpr int l = k * SK;
+                T x0 = n0, x1 = n1, xx2 = x2[k];
+                if constexpr (k + 1 < N1) {
+                    n0 = B[l + SK];
+                    n1 = A[l + SK];
+                }
                 T g[6];
                 T lam_out = T(1);  // GATHER 2: lambda applied to the outputs, after the energy
                 if constexpr (GEO == GEO_TRI) {
@@ -602,25 +571,25 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         // P4: D_r^T r in place on the r-pencils; D_s^T s into registers
         {
             T p[N1], o[N1];
-            rpencil_read<S>(B, ra, rb, p);
+            rpencil_read<L, N1>(Br, p);
             if constexpr ((s_hoist<N1, GEO, T>() & 2) != 0) {
                 T q[N1];
 #pragma unroll
-                for (int n = 0; n < N1; ++n) q[n] = A[S::pos(pa, n, pb)];
+                for (int n = 0; n < N1; ++n) q[n] = As[n * SJ];
                 bwd(p, o);
-                if (inslot) rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<L, N1>(Br, o);
                 bwd(q, o1);
             } else {
                 bwd(p, o);
-                if (inslot) rpencil_write<S>(B, ra, rb, o);
+                if (inslot) rpencil_write<L, N1>(Br, o);
 #pragma unroll
-                for (int n = 0; n < N1; ++n) p[n] = A[S::pos(pa, n, pb)];
+                for (int n = 0; n < N1; ++n) p[n] = As[n * SJ];
                 bwd(p, o1);
             }
             // each s-pencil is read and written by its own lane only
             if (inslot) {
 #pragma unroll
-                for (int a = 0; a < N1; ++a) A[S::pos(pa, a, pb)] = o1[a];
+                for (int a = 0; a < N1; ++a) As[a * SJ] = o1[a];
             }
         }
         group_sync<BLOCK>();
@@ -634,7 +603,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         if (active) {
             const Buf by(yb);
             each_node<N1>([&](auto k) {
-                const int l = S::pos(i, j, k);
+                constexpr int l = k * SK;
                 by.template store<k * NT * (int)sizeof(T), T>(lo, (B[l] + A[l]) + y2[k]);
             });
         }
@@ -797,16 +766,11 @@ static int dispatch(int N, int64_t E, int nrhs, const double* geo, const T* Gs, 
     switch (N + 1) {
 #define AX_CASE(n1) \
     case n1: return launch_n1<n1, GEO, T>(E, nrhs, geo, Gs, X, Y, D, xi, w, st, l2g, ldg, es, ccs, fo);
-#ifdef AX_FEW
-        AX_CASE(3) AX_CASE(4) AX_CASE(6) AX_CASE(7) AX_CASE(8) AX_CASE(9) AX_CASE(10) AX_CASE(12) AX_CASE(13) AX_CASE(16)
-    default: return fail(AX_ERR_UNSUPPORTED, "few");
-#else
         AX_CASE(2) AX_CASE(3) AX_CASE(4) AX_CASE(5) AX_CASE(6) AX_CASE(7) AX_CASE(8) AX_CASE(9)
         AX_CASE(10) AX_CASE(11) AX_CASE(12) AX_CASE(13) AX_CASE(14) AX_CASE(15) AX_CASE(16)
 #undef AX_CASE
     default:
         return fail(AX_ERR_UNSUPPORTED, "order N=%d outside [1,15]", N);
-#endif
     }
 }
 }  // namespace ax

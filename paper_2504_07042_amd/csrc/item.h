@@ -47,9 +47,9 @@ struct BShape {
     static constexpr int NP = Shape<N1>::NP;
     static_assert(EPB * NT <= BLOCK && BLOCK % 64 == 0 && BLOCK <= 1024, "item shape");
     template <typename T>
-    static constexpr int FS = Shape<N1, sizeof(T)>::FS;
+    static constexpr size_t field_bytes() { return ((size_t)TileLds<N1, EPB, sizeof(T)>::WORDS * sizeof(T) + 7) / 8 * 8; }
     template <typename T>
-    static constexpr size_t lds_bytes() { return (size_t)EPB * 2 * FS<T> * sizeof(T) + (size_t)EPB * 24 * 8; }
+    static constexpr size_t lds_bytes() { return field_bytes<T>() + (size_t)EPB * 24 * 8; }
 };
 
 // cs: source of the basis tables (CoefResident or CoefReload)
@@ -59,19 +59,24 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
                                              const T* __restrict__ lamp = nullptr)
 {
     using S = BShape<N1, V>;
-    constexpr int NT = S::NT, EPB = S::EPB, FS = S::template FS<T>, NP = S::NP;
+    using L = TileLds<N1, S::EPB, sizeof(T)>;
+    constexpr int NT = S::NT, EPB = S::EPB, NP = S::NP, SJ = L::SJ, SK = L::SK;
     T* smem = reinterpret_cast<T*>(lds);
-    double* svert = reinterpret_cast<double*>(lds + (size_t)EPB * 2 * FS * sizeof(T));
+    double* svert = reinterpret_cast<double*>(lds + S::template field_bytes<T>());
     const int tid = threadIdx.x;
     const int slot = tid / NT;
     const int lane = tid - slot * NT;
     const bool inslot = slot < EPB;
     const int64_t e = eb * EPB + slot;
     const bool active = inslot && e < m.E;
-    T* A = smem + (inslot ? slot : 0) * 2 * FS;
-    T* B = A + FS;
     const int i = lane % N1, j = lane / N1;
-    const int pa = i, pb = j;
+    // the two fields at this lane's home column, at its r-pencil and at its s-pencil (the pencils
+    // of any element of the group)
+    T* A = smem + (inslot ? slot : 0) * L::ST + j * SJ + i;
+    T* B = A + L::FS;
+    T* Ar = smem + L::pencils.r[inslot ? tid : 0];
+    T* Br = Ar + L::FS;
+    T* As = smem + L::pencils.s[inslot ? tid : 0];
     const T* X = reinterpret_cast<const T*>(m.X);
     T* Y = reinterpret_cast<T*>(m.Y);
 
@@ -112,20 +117,18 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         }
         if (inslot) {
 #pragma unroll
-            for (int k = 0; k < N1; ++k) A[Shape<N1, sizeof(T)>::pos(i, j, k)] = xr[k];
+            for (int k = 0; k < N1; ++k) A[k * SK] = xr[k];
         }
         contract<N1, false, true>(cs, xr, x2);
         lds_barrier();
         T o1[N1];
         if (inslot) {
             T p[N1], o[N1];
-#pragma unroll
-            for (int n = 0; n < N1; ++n) p[n] = A[Shape<N1, sizeof(T)>::pos(n, pa, pb)];
+            rpencil_read<L, N1>(Ar, p);
             contract<N1, false, true>(cs, p, o);
+            rpencil_write<L, N1>(Br, o);
 #pragma unroll
-            for (int a = 0; a < N1; ++a) B[Shape<N1, sizeof(T)>::pos(a, pa, pb)] = o[a];
-#pragma unroll
-            for (int n = 0; n < N1; ++n) p[n] = A[Shape<N1, sizeof(T)>::pos(pa, n, pb)];
+            for (int n = 0; n < N1; ++n) p[n] = As[n * SJ];
             contract<N1, false, true>(cs, p, o1);
         }
         // Partial recomputation: all N1 scale loads of the column issued before the barrier
@@ -142,14 +145,14 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         lds_barrier();
         if (inslot) {
 #pragma unroll
-            for (int a = 0; a < N1; ++a) A[Shape<N1, sizeof(T)>::pos(pa, a, pb)] = o1[a];
+            for (int a = 0; a < N1; ++a) As[a * SJ] = o1[a];
         }
         lds_barrier();
         T tt[N1];
         if (inslot) {
 #pragma unroll
             for (int k = 0; k < N1; ++k) {
-                const int l = Shape<N1, sizeof(T)>::pos(i, j, k);
+                const int l = k * SK;
                 T x0 = B[l], x1 = A[l], xx2 = x2[k];
                 T g[6], lam;
                 const C b = cs.row();
@@ -175,34 +178,30 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
         lds_barrier();
         if (inslot) {
             T p[N1], o[N1];
-#pragma unroll
-            for (int n = 0; n < N1; ++n) p[n] = B[Shape<N1, sizeof(T)>::pos(n, pa, pb)];
+            rpencil_read<L, N1>(Br, p);
             contract<N1, true, true>(cs, p, o);
+            rpencil_write<L, N1>(Br, o);
+            // each s-pencil is read and written by its own lane only
 #pragma unroll
-            for (int a = 0; a < N1; ++a) B[Shape<N1, sizeof(T)>::pos(a, pa, pb)] = o[a];
-#pragma unroll
-            for (int n = 0; n < N1; ++n) p[n] = A[Shape<N1, sizeof(T)>::pos(pa, n, pb)];
+            for (int n = 0; n < N1; ++n) p[n] = As[n * SJ];
             contract<N1, true, true>(cs, p, o1);
-        }
-        lds_barrier();
-        if (inslot) {
 #pragma unroll
-            for (int a = 0; a < N1; ++a) B[Shape<N1, sizeof(T)>::pos(pa, a, pb)] += o1[a];
+            for (int a = 0; a < N1; ++a) As[a * SJ] = o1[a];
         }
         lds_barrier();
         if (active) {
 #pragma unroll
-            for (int k = 0; k < N1; ++k) Y[base + i + j * N1 + k * NT] = B[Shape<N1, sizeof(T)>::pos(i, j, k)] + y2[k];
+            for (int k = 0; k < N1; ++k) Y[base + i + j * N1 + k * NT] = (B[k * SK] + A[k * SK]) + y2[k];
         }
-        lds_barrier();
+        // (no barrier: the next column or item first writes this lane's own home words, and the
+        // vertex table, last read before the barriers above)
     }
 }
 
 // The per-item path above as a single-mesh persistent kernel (no work list): work-group g takes
-// element groups g, g + grid, ...  Used by ax_local (and its partial-recomputation form) for the
-// trilinear orders whose register footprint the prefetching kernel exceeds (FP64 N1 = 9..15:
-// 118-162 VGPRs here against 256 plus spills there; measured 1.4-3.2x faster) or fills only at
-// two waves per SIMD (N1 = 6, 7), with the tables reloaded per output row; which kernel runs is
+// element groups g, g + grid, ...  Used by ax_local (and its partial-recomputation form) where it
+// is the faster kernel (FP32 N1 = 9 and 13..15, FP64 N1 = 7), with the tables reloaded per output
+// row; which kernel runs is
 // a run-time choice (item_default, or the tuning table).  V: shape variant (item_shape); W:
 // register budget variant (item_waves).
 template <typename T>
