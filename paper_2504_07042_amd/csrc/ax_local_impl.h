@@ -210,15 +210,16 @@ struct OneMeshWalk {
 // (one column, the CG's operator): as 1, and each work-group also writes the sum of its
 // elements' energies (D X_e)^T G_e (D X_e) = X_e^T Y_e to epart[blockIdx.x], which sums to
 // p^T A p when X = Q p and p vanishes on the masked nodes.  `cs` is the source of the
-// contraction coefficients (CoefResident, CoefReload or CoefConst).  Local vectors: node l of column c of
+// contraction coefficients (CoefResident, CoefReload or CoefConst), `bs` the basis as kernel
+// arguments or in constant memory.  Local vectors: node l of column c of
 // element e at c * ccs + e * es + l (es = N1^3, ccs = E N1^3 for [nrhs][E][N1^3];
 // es = nrhs N1^3, ccs = N1^3 for the component-interleaved [E][nrhs][N1^3] of a vector field).
 // With a work list `wl` (W::kList, trilinear only, es = N1^3) the element groups and their
 // addresses come from the list; E, geo, X, Y, l2g, ldg and ccs are then unused.
-template <int N1, int GEO, bool EO, int GATHER, int EPBX, bool ONE, typename T, typename C, typename W = OneMeshWalk>
+template <int N1, int GEO, bool EO, int GATHER, int EPBX, bool ONE, typename T, typename BS, typename C, typename W = OneMeshWalk>
 __device__ __forceinline__ void
 ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __restrict__ Gs,
-              const T* __restrict__ X, T* __restrict__ Y, const Basis<T>& bs,
+              const T* __restrict__ X, T* __restrict__ Y, const BS& bs,
               const int32_t* __restrict__ l2g, int64_t ldg, int64_t es, int64_t ccs, double* __restrict__ epart,
               const C& cs, const W& wl = W{})
 {
