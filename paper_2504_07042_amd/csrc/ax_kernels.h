@@ -67,16 +67,10 @@ constexpr int item_waves(int N1, bool fp32, bool partial, int alt)
 }
 
 // Which kernel runs when the tuning table says "auto" (measured on gfx950, GDOF/s at 2^24 nodes,
-// tile against per-item kernel).  FP64: the tile kernel (N1 = 5: 199 against 191; 6: 203, 194;
-// 9: 204, 171; 10: 174, 151; 13: 163, 142) except the full form at N1 = 7, where the two tie (205,
-// 200).  FP32: the per-item kernel at N1 = 13 (212, 257; partial form 215, 264) and, in the full
-// form, 9 (299, 306), 14 (195, 210) and 15 (199, 205); the tile kernel elsewhere (10: 290, 259; 12: 265,
-// 220).
-constexpr bool item_default(int N1, int geo, bool fp32)
-{
-    if (geo == GEO_TRI) return fp32 ? N1 == 9 || (N1 >= 13 && N1 <= 15) : N1 == 7;
-    return geo == GEO_TRIL && fp32 && N1 == 13;
-}
+// tile against per-item kernel).  The tile kernel (FP64 N1 = 6: 200 against 190; 9: 203, 177; 10:
+// 181, 161; FP32 9: 304, 305; 13: 274, 274; 15: 279, 268; partial form 13: 286, 282) except FP64 N1 = 7, full form, where
+// repeat runs put them 3 to 8 % apart (205-210, 194-200).
+constexpr bool item_default(int N1, int geo, bool fp32) { return geo == GEO_TRI && !fp32 && N1 == 7; }
 
 // Orders with a batched tile kernel (the single-mesh tile body walking the batch's work list):
 // FP64 up to N1 = 7, FP32 up to N1 = 10.  At FP64 N1 >= 8 the kernel spills (N1 = 8: 464-496
@@ -241,7 +235,7 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 // which a single-column kernel does not spill (a few registers at N1 = 4 and FP32 aside).  FP64:
 // four to N1 = 8, three above (natural use 110-168 VGPRs; 9 and 10 then run four), two for the
 // Helmholtz form from N1 = 12 (184-224 VGPRs, 15-60 spills at three).  N1 = 16 is held to two by
-// its LDS.  FP32: five (96 VGPRs) except the trilinear and Helmholtz forms to N1 = 12, four.
+// its LDS.  FP32: five (96 VGPRs); the trilinear form to N1 = 12 and the Helmholtz form, four.
 #ifndef AX_MINW_F64_LO
 #define AX_MINW_F64_LO 4
 #endif
@@ -254,7 +248,7 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 constexpr int tile_waves(int N1, int geo, bool fp32)
 {
     if (N1 == 16) return 2;
-    if (fp32) return (geo == GEO_TRI || geo == GEO_HELM) && N1 <= 12 ? AX_MINW_F32_TRI : 5;
+    if (fp32) return geo == GEO_HELM || (geo == GEO_TRI && N1 <= 12) ? AX_MINW_F32_TRI : 5;
     if (N1 <= 8) return geo == GEO_HELM && N1 == 4 ? 3 : AX_MINW_F64_LO;
     return geo == GEO_HELM && N1 >= 12 ? 2 : AX_MINW_F64_HI;
 }
@@ -267,9 +261,19 @@ constexpr int tile_waves(int N1, int geo, bool fp32)
 // file, where keeping them resident would spill them into vector-register lanes.
 template <typename T>
 struct CoefResident {
+    static constexpr bool kByRow = false;
     const Basis<T>& b;
     __device__ __forceinline__ CoefResident row() const { return *this; }
     __device__ __forceinline__ T D(int q) const { return b.D[q]; }
+    template <int H>
+    __device__ __forceinline__ void rows(int a, T* p, T* m) const
+    {
+#pragma unroll
+        for (int n = 0; n < H; ++n) {
+            p[n] = b.P[a * H + n];
+            m[n] = b.M[a * H + n];
+        }
+    }
     __device__ __forceinline__ T P(int q) const { return b.P[q]; }
     __device__ __forceinline__ T M(int q) const { return b.M[q]; }
     __device__ __forceinline__ T Cm(int q) const { return b.Cm[q]; }
@@ -285,6 +289,7 @@ using KargPtr = const __attribute__((address_space(4))) KA*;
 // table that the kernel only reads), which keeps the loads on the scalar unit.
 template <typename T>
 struct CoefReload {
+    static constexpr bool kByRow = true;  // transposed contractions walk the tables by rows
     KargPtr<Basis<T>> k;
     __device__ __forceinline__ CoefReload row() const
     {
@@ -293,12 +298,36 @@ struct CoefReload {
         return CoefReload{q};
     }
     __device__ __forceinline__ T D(int q) const { return k->D[q]; }
-    __device__ __forceinline__ T P(int q) const { return k->P[q]; }
-    __device__ __forceinline__ T M(int q) const { return k->M[q]; }
     __device__ __forceinline__ T Cm(int q) const { return k->Cm[q]; }
     __device__ __forceinline__ T Rm(int q) const { return k->Rm[q]; }
     __device__ __forceinline__ double xi(int q) const { return k->xi[q]; }
     __device__ __forceinline__ double w(int q) const { return k->w[q]; }
+    // row a of the H by H tables P and M
+    template <int H>
+    __device__ __forceinline__ void rows(int a, T* p, T* m) const
+    {
+        copy_row<H>(&k->P[a * H], p);
+        copy_row<H>(&k->M[a * H], m);
+    }
+    // in whole vectors, which run on into the next row or table (one scalar load of 16 or 32 bytes each)
+    template <int H>
+    static __device__ __forceinline__ void copy_row(KargPtr<T> q, T* r)
+    {
+        constexpr int V = sizeof(T) == 4 && H > 4 ? 8 : 4;
+        typedef T vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+#pragma unroll
+        for (int c = 0; c < H; c += V) {
+            if (H - c > V / 2) {
+                const vec v = *(KargPtr<vec>)(q + c);
+#pragma unroll
+                for (int n = 0; n < V; ++n)
+                    if (c + n < H) r[c + n] = v[n];
+            } else {
+#pragma unroll
+                for (int n = c; n < H; ++n) r[n] = q[n];
+            }
+        }
+    }
 };
 
 // Basis tables in device memory read through the constant address space and left to the
@@ -307,9 +336,19 @@ struct CoefReload {
 // kernel that receives them by pointer.
 template <typename T>
 struct CoefConst {
+    static constexpr bool kByRow = false;
     KargPtr<Basis<T>> k;
     __device__ __forceinline__ CoefConst row() const { return *this; }
     __device__ __forceinline__ T D(int q) const { return k->D[q]; }
+    template <int H>
+    __device__ __forceinline__ void rows(int a, T* p, T* m) const
+    {
+#pragma unroll
+        for (int n = 0; n < H; ++n) {
+            p[n] = k->P[a * H + n];
+            m[n] = k->M[a * H + n];
+        }
+    }
     __device__ __forceinline__ T P(int q) const { return k->P[q]; }
     __device__ __forceinline__ T M(int q) const { return k->M[q]; }
     __device__ __forceinline__ T Cm(int q) const { return k->Cm[q]; }
@@ -526,18 +565,48 @@ __device__ __forceinline__ void contract_eo(const C& src, const T* in, T* out)
         ue[n] = in[n] + in[N - n];
         uo[n] = in[n] - in[N - n];
     }
+    if constexpr (TRANS && C::kByRow) {
+        // all outputs advance by one row of the tables at a time: a row is contiguous, a column
+        // takes one scalar load per coefficient.  Each sum has its terms in the order it has below.
+        T e[H], o[H];
 #pragma unroll
-    for (int a = 0; a < H; ++a) {
-        const C c = src.row();
-        T e = T(0), o = T(0);
+        for (int a = 0; a < H; ++a) e[a] = o[a] = T(0);
 #pragma unroll
         for (int n = 0; n < H; ++n) {
-            e = fma(TRANS ? c.M(n * H + a) : c.P(a * H + n), ue[n], e);
-            o = fma(TRANS ? c.P(n * H + a) : c.M(a * H + n), uo[n], o);
+            T p[H], m[H];
+            src.row().template rows<H>(n, p, m);
+#pragma unroll
+            for (int a = 0; a < H; ++a) {
+                e[a] = fma(m[a], ue[n], e[a]);
+                o[a] = fma(p[a], uo[n], o[a]);
+            }
         }
-        if constexpr (N1 % 2 == 1) e = fma(TRANS ? c.Rm(a) : c.Cm(a), in[H], e);
-        out[a] = e + o;
-        out[N - a] = o - e;
+        const C c = src.row();
+#pragma unroll
+        for (int a = 0; a < H; ++a) {
+            if constexpr (N1 % 2 == 1) e[a] = fma(c.Rm(a), in[H], e[a]);
+            out[a] = e[a] + o[a];
+            out[N - a] = o[a] - e[a];
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < H; ++a) {
+            const C c = src.row();
+            T e = T(0), o = T(0), p[H], m[H];
+            if constexpr (!TRANS) c.template rows<H>(a, p, m);
+#pragma unroll
+            for (int n = 0; n < H; ++n) {
+                if constexpr (TRANS) {
+                    p[n] = c.M(n * H + a);
+                    m[n] = c.P(n * H + a);
+                }
+                e = fma(p[n], ue[n], e);
+                o = fma(m[n], uo[n], o);
+            }
+            if constexpr (N1 % 2 == 1) e = fma(TRANS ? c.Rm(a) : c.Cm(a), in[H], e);
+            out[a] = e + o;
+            out[N - a] = o - e;
+        }
     }
     if constexpr (N1 % 2 == 1) {
         const C c = src.row();
@@ -545,6 +614,12 @@ __device__ __forceinline__ void contract_eo(const C& src, const T* in, T* out)
 #pragma unroll
         for (int n = 0; n < H; ++n) m = fma(TRANS ? c.Cm(n) : c.Rm(n), uo[n], m);
         out[H] = m;
+    }
+    // the products are formed here: moved under the condition of their use by the compiler they
+    // would leave the loads behind, and all rows of the tables in registers
+    if constexpr (C::kByRow) {
+#pragma unroll
+        for (int a = 0; a < N1; ++a) asm volatile("" : "+v"(out[a]));
     }
 }
 

@@ -200,8 +200,7 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
 
 // The per-item path above as a single-mesh persistent kernel (no work list): work-group g takes
 // element groups g, g + grid, ...  Used by ax_local (and its partial-recomputation form) where it
-// is the faster kernel (FP32 N1 = 9 and 13..15, FP64 N1 = 7), with the tables reloaded per output
-// row; which kernel runs is
+// is the default (item_default), with the tables reloaded row by row; which kernel runs is
 // a run-time choice (item_default, or the tuning table).  V: shape variant (item_shape); W:
 // register budget variant (item_waves).
 template <typename T>
