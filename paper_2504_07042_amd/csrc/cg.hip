@@ -53,13 +53,19 @@ struct CgScal {
     int converged;  // 1 once r . r <= tol2
     int breakdown;  // 1 on p^T A p <= 0 or a non-finite scalar
     int iters;
-    int pad;
+    // the state between the two halves of an iteration: written by update_dot_kernel from rz,
+    // converged and breakdown, turned into the next ones by cg_dir_kernel (so that no kernel
+    // writes what its other work-groups read)
+    int mid_converged;
+    int mid_breakdown;
+    double mid_rz;
 };
 
-// Partial sums of the fixed-grid reductions: [2][nrhs][kRedBlocks], the second half for r . z.
+// Partial sums of the fixed-grid reductions: [3][nrhs][kRedBlocks]: r . r (and other dot products),
+// r . z and, of the iteration, p . A p.
 
 // Sums of v over the work-group, for M values at once, in a fixed order: each wave by halves
-// through register shuffles, then the waves in order.  One barrier; every thread has the sums.
+// through register shuffles, then the waves in order.  Every thread has the sums.
 template <int THREADS, int M>
 __device__ __forceinline__ void block_sum(double (&v)[M])
 {
@@ -77,20 +83,38 @@ __device__ __forceinline__ void block_sum(double (&v)[M])
 #pragma unroll
         for (int w = 1; w < THREADS / 64; ++w) v[m] += part[m][w];
     }
+    __syncthreads();  // (the kernel may sum again)
 }
 
-// Calls f(q) for this thread's elements of [0, n), kVecUnroll of them at a time with `full` set
-// where all are in range, so that their loads are in flight together.
+// Runs over this work-group's tiles of [0, n), kVecUnroll elements per thread: load(regs, q), then
+// use(regs, q), with R<U> the registers of U elements q, q + kRedThreads, ...  `first` runs between
+// the two on the first tile (and in work-groups without a tile): what it waits for overlaps that
+// tile's loads.
 constexpr int kVecUnroll = 4;
-template <typename F>
-__device__ __forceinline__ void each_tile(int64_t n, F&& f)
+constexpr int64_t kVecTile = (int64_t)kRedThreads * kVecUnroll;
+template <template <int> class R, typename F, typename L, typename U>
+__device__ __forceinline__ void each_tile(int64_t n, F&& first, L&& load, U&& use)
 {
-    constexpr int64_t TILE = (int64_t)kRedThreads * kVecUnroll;
-    for (int64_t q0 = (int64_t)blockIdx.x * TILE; q0 < n; q0 += (int64_t)gridDim.x * TILE) {
-        if (q0 + TILE <= n)
-            f(std::integral_constant<int, kVecUnroll>{}, q0 + threadIdx.x);
-        else
-            for (int64_t q = q0 + threadIdx.x; q < n; q += kRedThreads) f(std::integral_constant<int, 1>{}, q);
+    int64_t q0 = (int64_t)blockIdx.x * kVecTile;
+    R<kVecUnroll> t;
+    const bool whole = q0 + kVecTile <= n;
+    if (whole) load(t, q0 + threadIdx.x);
+    first();
+    if (whole) {
+        use(t, q0 + threadIdx.x);
+        q0 += (int64_t)gridDim.x * kVecTile;
+    }
+    for (; q0 < n; q0 += (int64_t)gridDim.x * kVecTile) {
+        if (q0 + kVecTile <= n) {
+            load(t, q0 + threadIdx.x);
+            use(t, q0 + threadIdx.x);
+        } else {
+            for (int64_t q = q0 + threadIdx.x; q < n; q += kRedThreads) {
+                R<1> e;
+                load(e, q);
+                use(e, q);
+            }
+        }
     }
 }
 
@@ -110,40 +134,40 @@ dot_partial_kernel(const TA* __restrict__ a, const TB* __restrict__ b, int64_t n
     if (threadIdx.x == 0) partials[c * kRedBlocks + blockIdx.x] = s[0];
 }
 
-// Sum of one column's partials, by kScalThreads threads; s2: of a second set too (s2 = s if null)
+// Sum of one column's partials, by THREADS threads; s2: of a second set too (s2 = s if null)
+template <int THREADS>
 __device__ __forceinline__ void sum_partials(const double* partials, const double* partials2, double& s, double& s2)
 {
-    constexpr int M = kRedBlocks / kScalThreads;
-    static_assert(M * kScalThreads == kRedBlocks, "whole rounds");
+    constexpr int M = kRedBlocks / THREADS;
+    static_assert(M * THREADS == kRedBlocks, "whole rounds");
     double v[2] = {0.0, 0.0}, a[M], b[M];
 #pragma unroll
     for (int q = 0; q < M; ++q) {
-        a[q] = partials[threadIdx.x + q * kScalThreads];
-        b[q] = partials2 ? partials2[threadIdx.x + q * kScalThreads] : 0.0;
+        a[q] = partials[threadIdx.x + q * THREADS];
+        b[q] = partials2 ? partials2[threadIdx.x + q * THREADS] : 0.0;
     }
 #pragma unroll
     for (int q = 0; q < M; ++q) {
         v[0] += a[q];
         v[1] += b[q];
     }
-    block_sum<kScalThreads>(v);
+    block_sum<THREADS>(v);
     s = v[0];
     s2 = partials2 ? v[1] : s;
 }
 
-// mode 0: rr = sum (initial), converged if rr <= tol2.   mode 1: alpha = rr / sum (= p.Ap).
-// mode 2: rr_new = sum; beta = rr_new / rr; rr = rr_new; converged test.
+// mode 0: rr = sum (initial), converged if rr <= tol2.
 // mode 3: rr = sum after a reliable update (alpha, beta and the iteration count are kept).
 // mode 4: sum = d . d of the iterate about to be folded; flags a non-finite one (breakdown 2).
-// With `pre` the partials hold r . r in the first and r . z in the second half (modes 0, 2, 3);
+// With `pre` the partials hold r . r in the first and r . z in the second part (modes 0, 3);
 // without, r . z = r . r.
 __global__ void __launch_bounds__(kScalThreads)
 cg_scalar_kernel(const double* __restrict__ partials, CgScal* __restrict__ sc, int mode, int pre)
 {
     const int c = blockIdx.x, nrhs = gridDim.x;
     double s, s2;
-    sum_partials(partials + c * kRedBlocks,
-                 pre && mode != 1 && mode != 4 ? partials + (size_t)nrhs * kRedBlocks + c * kRedBlocks : nullptr, s, s2);
+    sum_partials<kScalThreads>(partials + c * kRedBlocks,
+                               pre && mode != 4 ? partials + ((size_t)nrhs + c) * kRedBlocks : nullptr, s, s2);
     if (threadIdx.x != 0) return;
     CgScal& q = sc[c];
     if (mode == 0) {
@@ -153,36 +177,68 @@ cg_scalar_kernel(const double* __restrict__ partials, CgScal* __restrict__ sc, i
         q.breakdown = isfinite(s) && isfinite(s2) ? 0 : 1;
         q.iters = 0;
         q.alpha = q.beta = 0.0;
-    } else if (mode == 1) {
-        if (q.converged || q.breakdown) {
-            q.alpha = 0.0;
-        } else if (!(s > 0.0) || !isfinite(s)) {
-            q.breakdown = 1;
-            q.alpha = 0.0;
-        } else {
-            q.alpha = q.rz / s;
-        }
     } else if (mode == 4) {
         // s = d . d of the reduced-precision iterate: a non-finite one must not reach x
         if (!isfinite(s)) q.breakdown = 2;
-    } else if (mode == 3) {
+    } else {
         // the iterated residual was replaced by the true one: new r . r, keep the iteration count
         q.rr = s;
         q.rz = s2;
         q.converged = (s <= q.tol2) ? 1 : 0;
         q.breakdown = isfinite(s) && isfinite(s2) ? 0 : 1;
-    } else {
-        if (q.converged || q.breakdown) {
-            q.beta = 0.0;
-        } else {
-            q.beta = s2 / q.rz;
-            q.rz = s2;
-            q.rr = s;
-            q.iters += 1;
-            if (!isfinite(s) || !isfinite(s2)) q.breakdown = 1;
-            else if (s <= q.tol2) q.converged = 1;
+    }
+}
+
+// alpha = r.z / p.Ap of column c, by every work-group of update_dot_kernel from the partials of
+// p . Ap; the first one leaves it and the flags in the state.
+__device__ __forceinline__ double cg_alpha(const double* pap, CgScal* q, int c)
+{
+    double s, unused;
+    sum_partials<kRedThreads>(pap + c * kRedBlocks, nullptr, s, unused);
+    const double rz = q->rz;
+    const int converged = q->converged;
+    int breakdown = q->breakdown;
+    double al = 0.0;
+    if (!converged && !breakdown) {
+        if (!(s > 0.0) || !isfinite(s)) breakdown = 1;
+        else al = rz / s;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        q->alpha = al;
+        q->mid_rz = rz;
+        q->mid_converged = converged;
+        q->mid_breakdown = breakdown;
+    }
+    return al;
+}
+
+// The end of the iteration, by every work-group of cg_dir_kernel from the partials of r . r and
+// (`pre`) r . z: beta = r.z / (r.z before), the convergence test; true if the column goes on.
+__device__ __forceinline__ bool cg_beta(const double* partials, CgScal* q, int c, bool pre, double& beta)
+{
+    double s, s2;
+    sum_partials<kRedThreads>(partials + c * kRedBlocks,
+                              pre ? partials + ((size_t)gridDim.y + c) * kRedBlocks : nullptr, s, s2);
+    const double rz = q->mid_rz;
+    int converged = q->mid_converged, breakdown = q->mid_breakdown;
+    const bool step = !converged && !breakdown;
+    beta = 0.0;
+    if (step) {
+        beta = s2 / rz;
+        if (!isfinite(s) || !isfinite(s2)) breakdown = 1;
+        else if (s <= q->tol2) converged = 1;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        q->beta = beta;
+        q->converged = converged;
+        q->breakdown = breakdown;
+        if (step) {
+            q->rz = s2;
+            q->rr = s;
+            q->iters += 1;
         }
     }
+    return !converged && !breakdown;
 }
 
 // The solver's view of Q^T: per global node its local copies (ascending local id), built once per
@@ -300,48 +356,65 @@ __device__ __forceinline__ void store_partials(double acc, double acz, bool pre,
     if (pre) partials[((size_t)gridDim.y + blockIdx.y) * kRedBlocks + blockIdx.x] = v[1];
 }
 
+// Registers of U elements (update_dot_kernel, cg_dir_kernel).
+template <typename TX, typename T>
+struct UpdateRegs {
+    template <int N>
+    struct Of {
+        static constexpr int U = N;
+        T r[N], ap[N], p[N], d[N];
+        TX x[N];
+    };
+};
+
 // Bound by memory (or the last-level cache).  10^6 FP64 values, update and both scalar kernels:
-// 12.4 + 2 x 6.2 us with one value per thread and LDS trees of 8 barriers, 10.0 + 2 x 4.5 as here.
+// 12.4 + 2 x 6.2 us with one value per thread and LDS trees of 8 barriers, 10.0 + 2 x 4.5 with
+// kVecUnroll values and block_sum; with the scalars computed by the kernels that use them, behind
+// the loads of the first tile, update 11.6 and direction 6.2 (from 5.4), no scalar kernel.
 // r -= alpha Ap and, with XUPD, x += alpha p; partial sums of r . r and, with the Jacobi
 // preconditioner (dinv != NULL), of r . z with z = dinv o r (fixed grid).  Without XUPD the x
 // update is left to cg_dir_kernel, which reads p anyway (see merged_x_update).
 template <typename TX, typename T, bool XUPD>
-__global__ void __launch_bounds__(kRedThreads)
+__global__ void __launch_bounds__(kRedThreads, 8)
 update_dot_kernel(TX* __restrict__ x, T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ Ap,
-                  const CgScal* __restrict__ sc, int64_t n, const T* __restrict__ dinv, double* __restrict__ partials)
+                  CgScal* __restrict__ sc, int64_t n, const T* __restrict__ dinv, const double* __restrict__ pap,
+                  double* __restrict__ partials)
 {
     const int c = blockIdx.y;
-    const double al = sc[c].alpha;
     const int64_t o = (int64_t)c * n;
-    double acc = 0.0, acz = 0.0;
-    each_tile(n, [&](auto U, int64_t q) {
-        T rv[U], av[U], pv[U], dv[U];
-        TX xv[U];
+    double al = 0.0, acc = 0.0, acz = 0.0;
+    each_tile<UpdateRegs<TX, T>::template Of>(
+        n,
+        [&] {
+            // (work-groups without a tile have no use for alpha; the first one writes the state)
+            if (blockIdx.x == 0 || (int64_t)blockIdx.x * kVecTile < n) al = cg_alpha(pap, sc + c, c);
+        },
+        [&](auto& t, int64_t q) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t g = q + u * kRedThreads;
-            rv[u] = r[o + g];
-            if (al != 0.0) {
-                av[u] = Ap[o + g];
+            for (int u = 0; u < t.U; ++u) {
+                const int64_t g = q + u * kRedThreads;
+                t.r[u] = r[o + g];
+                t.ap[u] = Ap[o + g];
                 if constexpr (XUPD) {
-                    pv[u] = p[o + g];
-                    xv[u] = x[o + g];
+                    t.p[u] = p[o + g];
+                    t.x[u] = x[o + g];
                 }
+                if (dinv) t.d[u] = dinv[g];
             }
-            if (dinv) dv[u] = dinv[g];
-        }
+        },
+        [&](auto& t, int64_t q) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t g = q + u * kRedThreads;
-            if (al != 0.0) {
-                if constexpr (XUPD) x[o + g] = (TX)((double)xv[u] + al * (double)pv[u]);
-                rv[u] = (T)((double)rv[u] - al * (double)av[u]);
-                r[o + g] = rv[u];
+            for (int u = 0; u < t.U; ++u) {
+                const int64_t g = q + u * kRedThreads;
+                if (al != 0.0) {
+                    if constexpr (XUPD) x[o + g] = (TX)((double)t.x[u] + al * (double)t.p[u]);
+                    t.r[u] = (T)((double)t.r[u] - al * (double)t.ap[u]);
+                    r[o + g] = t.r[u];
+                }
+                acc = fma((double)t.r[u], (double)t.r[u], acc);
+                if (dinv) acz = fma((double)t.r[u] * (double)t.d[u], (double)t.r[u], acz);
             }
-            acc = fma((double)rv[u], (double)rv[u], acc);
-            if (dinv) acz = fma((double)rv[u] * (double)dv[u], (double)rv[u], acz);
-        }
-    });
+        });
     store_partials(acc, acz, dinv != nullptr, partials);
 }
 
@@ -386,42 +459,45 @@ invert_diag_kernel(double* __restrict__ dinv, float* __restrict__ dinv32, const 
 // With XUPD, x += alpha p with this iteration's p (whenever alpha != 0, as the r update pairs
 // it); then p = z + beta p, z = dinv o r (dinv != NULL) or r, unless the column has converged or
 // broken down.  Grid and tiles of update_dot_kernel and qt_dot_kernel, so that an XCD reads what it
-// has written itself (10^6 FP64 values: 7.6 us with tiles of 256, 5.4 with these)
+// has written itself (10^6 FP64 values: 7.6 us with tiles of 256, 5.4 with these, without the sums)
 template <typename TX, typename T, bool XUPD>
-__global__ void __launch_bounds__(kRedThreads)
-cg_dir_kernel(TX* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, const CgScal* __restrict__ sc,
-              int64_t n, const T* __restrict__ dinv)
+__global__ void __launch_bounds__(kRedThreads, 8)
+cg_dir_kernel(TX* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, CgScal* __restrict__ sc, int64_t n,
+              const T* __restrict__ dinv, const double* __restrict__ partials)
 {
     const int c = blockIdx.y;
-    const bool dir = !(sc[c].converged || sc[c].breakdown);
-    const double be = sc[c].beta, al = XUPD ? sc[c].alpha : 0.0;
     const int64_t o = (int64_t)c * n;
-    if (al == 0.0 && !dir) return;
-    each_tile(n, [&](auto U, int64_t q) {
-        T pv[U], rv[U], dv[U];
-        TX xv[U];
+    const double al = XUPD ? sc[c].alpha : 0.0;
+    double be = 0.0;
+    bool dir = false;
+    each_tile<UpdateRegs<TX, T>::template Of>(
+        n,
+        [&] {
+            if (blockIdx.x == 0 || (int64_t)blockIdx.x * kVecTile < n)
+                dir = cg_beta(partials, sc + c, c, dinv != nullptr, be);
+        },
+        [&](auto& t, int64_t q) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t g = q + u * kRedThreads;
-            pv[u] = p[o + g];
-            if (dir) {
-                rv[u] = r[o + g];
-                if (dinv) dv[u] = dinv[g];
+            for (int u = 0; u < t.U; ++u) {
+                const int64_t g = q + u * kRedThreads;
+                t.p[u] = p[o + g];
+                t.r[u] = r[o + g];
+                if (dinv) t.d[u] = dinv[g];
+                if constexpr (XUPD) t.x[u] = x[o + g];
             }
-            if constexpr (XUPD)
-                if (al != 0.0) xv[u] = x[o + g];
-        }
+        },
+        [&](auto& t, int64_t q) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t g = q + u * kRedThreads;
-            if constexpr (XUPD)
-                if (al != 0.0) x[o + g] = (TX)((double)xv[u] + al * (double)pv[u]);
-            if (dir) {
-                const double z = dinv ? (double)dv[u] * (double)rv[u] : (double)rv[u];
-                p[o + g] = (T)(z + be * (double)pv[u]);
+            for (int u = 0; u < t.U; ++u) {
+                const int64_t g = q + u * kRedThreads;
+                if constexpr (XUPD)
+                    if (al != 0.0) x[o + g] = (TX)((double)t.x[u] + al * (double)t.p[u]);
+                if (dir) {
+                    const double z = dinv ? (double)t.d[u] * (double)t.r[u] : (double)t.r[u];
+                    p[o + g] = (T)(z + be * (double)t.p[u]);
+                }
             }
-        }
-    });
+        });
 }
 
 // r = b - Ax (FP64).  Entries under the Dirichlet mask come out 0 because Ax is 0 there and the
@@ -512,7 +588,7 @@ set_tol_kernel(CgScal* sc, const double* __restrict__ partials, double rtol)
 {
     const int c = blockIdx.x;
     double bb, unused;
-    sum_partials(partials + c * kRedBlocks, nullptr, bb, unused);
+    sum_partials<kScalThreads>(partials + c * kRedBlocks, nullptr, bb, unused);
     if (threadIdx.x == 0) {
         sc[c].tol2 = rtol * rtol * bb;
         sc[c].converged = 0;
@@ -544,7 +620,7 @@ struct CgWork {
     double *pl, *wl;               // FP64 local vectors [nrhs][nl]
     float *b32, *r32, *p32, *Ap32, *d32; // inner global vectors
     float *pl32, *wl32;            // inner local vectors
-    double* partials;              // [2][nrhs][kRedBlocks]
+    double* partials;              // [3][nrhs][kRedBlocks]
     double* dinv;                  // Jacobi preconditioner [n_global] (or NULL)
     float* dinv32;                 // its float copy for the reduced-precision recurrences
     CopyPair* pairs;               // [n_global]
@@ -573,7 +649,7 @@ static void carve(Carver& cv, int64_t nl, int64_t ng, int nrhs, bool mixed, bool
     } else {
         w.b32 = w.r32 = w.p32 = w.Ap32 = w.d32 = w.pl32 = w.wl32 = nullptr;
     }
-    w.partials = cv.take<double>((size_t)2 * kRedBlocks * nrhs);
+    w.partials = cv.take<double>((size_t)3 * kRedBlocks * nrhs);
     w.dinv = pre ? cv.take<double>(ng) : nullptr;
     w.dinv32 = (pre && mixed) ? cv.take<float>(ng) : nullptr;
     w.pairs = cv.take<CopyPair>(ng);
@@ -717,6 +793,7 @@ static int cg_block(const Operator& op, int nrhs, int prec, TX* x, T* r, T* p, T
 {
     const int64_t ng = op.n_global;
     const T* dinv = op_dinv<T>(op);
+    double* pap = partials + (size_t)2 * kRedBlocks * nrhs;  // p . Ap
     const bool merged = merged_x_update(ng * nrhs * (int64_t)sizeof(T));
     const bool fused = nrhs == 1 && fused_operator(op, prec);
     for (int q = 0; q < count; ++q) {
@@ -726,7 +803,7 @@ static int cg_block(const Operator& op, int nrhs, int prec, TX* x, T* r, T* p, T
                 FusedOut fo{op.epart, op.epart_cap, 0};
                 AX_TRY(ax_local_gather_fused(*op.p, p, ng, wl, &fo, st));
                 hipLaunchKernelGGL((qt_dot_kernel<T, true>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0, st, ng,
-                                   op.pairs, op.gidx, op.n_local, wl, p, Ap, partials, op.epart,
+                                   op.pairs, op.gidx, op.n_local, wl, p, Ap, pap, op.epart,
                                    fo.nparts);
             } else {
                 return fail(AX_ERR_ARG, "internal: the fused operator is FP32");
@@ -734,22 +811,20 @@ static int cg_block(const Operator& op, int nrhs, int prec, TX* x, T* r, T* p, T
         } else {
             AX_TRY(apply_local<T>(op, nrhs, prec, p, pl, wl, st));
             hipLaunchKernelGGL((qt_dot_kernel<T, false>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0, st, ng,
-                               op.pairs, op.gidx, op.n_local, wl, p, Ap, partials, nullptr, 0);
+                               op.pairs, op.gidx, op.n_local, wl, p, Ap, pap, nullptr, 0);
         }
-        AX_TRY(scal(partials, sc, 1, nrhs, st));
         if (merged)
             hipLaunchKernelGGL((update_dot_kernel<TX, T, false>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0,
-                               st, x, r, p, Ap, sc, ng, dinv, partials);
+                               st, x, r, p, Ap, sc, ng, dinv, pap, partials);
         else
             hipLaunchKernelGGL((update_dot_kernel<TX, T, true>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0,
-                               st, x, r, p, Ap, sc, ng, dinv, partials);
-        AX_TRY(scal(partials, sc, 2, nrhs, st, dinv != nullptr));
+                               st, x, r, p, Ap, sc, ng, dinv, pap, partials);
         if (merged)
             hipLaunchKernelGGL((cg_dir_kernel<TX, T, true>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0, st, x, p, r,
-                               sc, ng, dinv);
+                               sc, ng, dinv, partials);
         else
             hipLaunchKernelGGL((cg_dir_kernel<TX, T, false>), dim3(kRedBlocks, nrhs), dim3(kRedThreads), 0, st, x, p, r,
-                               sc, ng, dinv);
+                               sc, ng, dinv, partials);
     }
     return hip_check(hipGetLastError(), "cg iteration");
 }

@@ -300,3 +300,24 @@ def test_jacobi_batched_cg_union(ax, inner):
         r = rhss[q] - oracle.apply_A(N, D, G, l2gq, ngq, maskq, xq)
         r2 += float(r @ r)
     assert np.sqrt(r2) / np.linalg.norm(b) <= 1e-10
+
+
+# The vector kernels of an iteration take tiles of 1024 values, 2048 tiles at a time: one short of a
+# tile, a tile, one more (two columns; with and without the preconditioner), the x update moved into
+# the direction kernel (vectors above 64 MiB), and a second round of tiles.
+@pytest.mark.parametrize("grid,nrhs,jacobi", [((2, 10, 30), 2, False), ((7, 7, 15), 2, True), ((4, 4, 40), 2, False),
+                                              ((40, 40, 40), 128, True), ((128, 127, 129), 1, True)])
+def test_cg_tile_edges(ax, grid, nrhs, jacobi):
+    import torch
+    m = meshgen.jittered_hex(*grid, alpha=0.1, seed=4)
+    l2g, ng, mask = meshgen.global_numbering(*grid, 1)
+    prob = ax.Problem(torch.from_numpy(m.verts).cuda(), ax.Basis(1), ax.GatherScatter(l2g, ng, mask))
+    g = torch.Generator("cuda").manual_seed(9)
+    b = torch.rand((nrhs, ng), dtype=torch.float64, device="cuda", generator=g) - 0.5
+    b[:, torch.from_numpy(np.asarray(mask)).cuda().bool()] = 0.0
+    x, rep = ax.cg_solve(prob, b, rtol=1e-10, precond=ax.AX_PRECOND_JACOBI if jacobi else ax.AX_PRECOND_NONE)
+    assert rep["status"] == "AX_OK", rep
+    # the recurrence stops at 1e-10 and drifts from the true residual by rounding (about
+    # iterations times 2^-53 times the growth of the iterates, below 1e-12 here)
+    r = b - prob.apply(x)
+    assert float((r.norm(dim=1) / b.norm(dim=1)).max()) <= 2e-10
