@@ -148,10 +148,26 @@ def _np_ptr(a: np.ndarray):
     return ctypes.c_void_p(a.ctypes.data)
 
 
+_Bytes = ctypes.c_char * 0
+
+
+def _np_arg(a: np.ndarray):
+    """The array's data as a call argument: through the buffer protocol (0.2 us, against 0.65 us for
+    the address), which read-only and strided arrays do not offer."""
+    try:
+        return _Bytes.from_buffer(a)
+    except (TypeError, ValueError, BufferError):
+        return _np_ptr(a)
+
+
 def _stream(stream=None):
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    if not torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle itself: 0.2 us, against 3 us for the Stream object around it
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _dptr(t):
@@ -202,8 +218,8 @@ def ax_local(X, geo, basis: Basis, geom=AX_TRILINEAR, prec=AX_FP64, out=None, st
     nrhs = _nrhs(X, E, basis.N)
     assert X.dtype == _prec_dtype(prec) and geo.dtype == torch.float64
     Y = torch.empty_like(X) if out is None else out
-    _check(lib().ax_local(E, basis.N, geom, _dptr(geo), _np_ptr(basis.D), _np_ptr(basis.xi),
-                          _np_ptr(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
+    _check(lib().ax_local(E, basis.N, geom, _dptr(geo), _np_arg(basis.D), _np_arg(basis.xi),
+                          _np_arg(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
     return Y
 
 
@@ -215,8 +231,8 @@ def ax_local_vector(X, geo, basis: Basis, geom=AX_TRILINEAR, prec=AX_FP64, out=N
     assert X.dim() == 3 and X.shape[0] == E and X.shape[1] == 3 and X.shape[2] == (basis.N + 1) ** 3
     assert X.dtype == _prec_dtype(prec) and geo.dtype == torch.float64
     Y = torch.empty_like(X) if out is None else out
-    _check(lib().ax_local_vector(E, basis.N, geom, _dptr(geo), _np_ptr(basis.D), _np_ptr(basis.xi),
-                                 _np_ptr(basis.w), prec, _dptr(X), _dptr(Y), _stream(stream)))
+    _check(lib().ax_local_vector(E, basis.N, geom, _dptr(geo), _np_arg(basis.D), _np_arg(basis.xi),
+                                 _np_arg(basis.w), prec, _dptr(X), _dptr(Y), _stream(stream)))
     return Y
 
 
@@ -230,8 +246,8 @@ def ax_local_gathered(Xg, l2g, geo, basis: Basis, geom=AX_TRILINEAR, prec=AX_FP6
     nrhs = Xg.shape[0] if Xg.dim() == 2 else 1
     assert Xg.dtype == _prec_dtype(prec) and l2g.dtype == torch.int32 and l2g.numel() == E * NP
     Y = torch.empty((nrhs, E, NP), dtype=Xg.dtype, device=Xg.device) if out is None else out
-    _check(lib().ax_local_gathered(E, basis.N, geom, _dptr(geo), _np_ptr(basis.D), _np_ptr(basis.xi),
-                                   _np_ptr(basis.w), nrhs, prec, _dptr(l2g), ng, _dptr(Xg), _dptr(Y),
+    _check(lib().ax_local_gathered(E, basis.N, geom, _dptr(geo), _np_arg(basis.D), _np_arg(basis.xi),
+                                   _np_arg(basis.w), nrhs, prec, _dptr(l2g), ng, _dptr(Xg), _dptr(Y),
                                    _stream(stream)))
     return Y
 
@@ -246,8 +262,8 @@ def ax_local_gathered_energy(Xg, l2g, geo, basis: Basis, geom=AX_TRILINEAR, stre
     Y = torch.empty((E, NP), dtype=torch.float32, device=Xg.device)
     work = torch.empty(max(E, 1), dtype=torch.float64, device=Xg.device)
     energy = torch.empty(1, dtype=torch.float64, device=Xg.device)
-    _check(lib().ax_local_gathered_energy(E, basis.N, geom, _dptr(geo), _np_ptr(basis.D), _np_ptr(basis.xi),
-                                          _np_ptr(basis.w), _dptr(l2g), Xg.shape[0], _dptr(Xg), _dptr(Y),
+    _check(lib().ax_local_gathered_energy(E, basis.N, geom, _dptr(geo), _np_arg(basis.D), _np_arg(basis.xi),
+                                          _np_arg(basis.w), _dptr(l2g), Xg.shape[0], _dptr(Xg), _dptr(Y),
                                           _dptr(work), _dptr(energy), _stream(stream)))
     return Y, energy
 
@@ -259,7 +275,7 @@ def ax_local_precomputedG(X, G, basis: Basis, prec=AX_FP64, out=None, stream=Non
     nrhs = _nrhs(X, E, basis.N)
     assert X.dtype == _prec_dtype(prec) and G.dtype == _prec_dtype(prec)
     Y = torch.empty_like(X) if out is None else out
-    _check(lib().ax_local_precomputedG(E, basis.N, _dptr(G), _np_ptr(basis.D), nrhs, prec,
+    _check(lib().ax_local_precomputedG(E, basis.N, _dptr(G), _np_arg(basis.D), nrhs, prec,
                                        _dptr(X), _dptr(Y), _stream(stream)))
     return Y
 
@@ -272,8 +288,8 @@ def ax_local_partial(X, verts, lam, basis: Basis, prec=AX_FP64, out=None, stream
     nrhs = _nrhs(X, E, basis.N)
     assert X.dtype == _prec_dtype(prec) and lam.dtype == _prec_dtype(prec) and verts.dtype == torch.float64
     Y = torch.empty_like(X) if out is None else out
-    _check(lib().ax_local_partial(E, basis.N, _dptr(verts), _dptr(lam), _np_ptr(basis.D), _np_ptr(basis.xi),
-                                  _np_ptr(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
+    _check(lib().ax_local_partial(E, basis.N, _dptr(verts), _dptr(lam), _np_arg(basis.D), _np_arg(basis.xi),
+                                  _np_arg(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
     return Y
 
 
@@ -285,8 +301,8 @@ def ax_local_helmholtz(X, verts, L23, basis: Basis, prec=AX_FP64, out=None, stre
     nrhs = _nrhs(X, E, basis.N)
     assert X.dtype == _prec_dtype(prec) and L23.dtype == _prec_dtype(prec) and verts.dtype == torch.float64
     Y = torch.empty_like(X) if out is None else out
-    _check(lib().ax_local_helmholtz(E, basis.N, _dptr(verts), _dptr(L23), _np_ptr(basis.D), _np_ptr(basis.xi),
-                                    _np_ptr(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
+    _check(lib().ax_local_helmholtz(E, basis.N, _dptr(verts), _dptr(L23), _np_arg(basis.D), _np_arg(basis.xi),
+                                    _np_arg(basis.w), nrhs, prec, _dptr(X), _dptr(Y), _stream(stream)))
     return Y
 
 
@@ -299,7 +315,7 @@ def helmholtz_factors(verts, lambda0, lambda1, basis: Basis, prec=AX_FP64, strea
     assert lambda0.shape == (E, NP) and lambda1.shape == (E, NP)
     assert lambda0.dtype == torch.float64 and lambda1.dtype == torch.float64
     L23 = torch.empty((E, 2, NP), dtype=_prec_dtype(prec), device=verts.device)
-    _check(lib().ax_helmholtz_factors(E, basis.N, _dptr(verts), _np_ptr(basis.xi), _np_ptr(basis.w),
+    _check(lib().ax_helmholtz_factors(E, basis.N, _dptr(verts), _np_arg(basis.xi), _np_arg(basis.w),
                                       _dptr(lambda0), _dptr(lambda1), prec, _dptr(L23), _stream(stream)))
     return L23
 
@@ -309,7 +325,7 @@ def geom_lambda(verts, basis: Basis, prec=AX_FP64, stream=None):
     import torch
     E = verts.shape[0]
     lam = torch.empty((E, (basis.N + 1) ** 3), dtype=_prec_dtype(prec), device=verts.device)
-    _check(lib().ax_geom_lambda(E, basis.N, _dptr(verts), _np_ptr(basis.xi), _np_ptr(basis.w), prec,
+    _check(lib().ax_geom_lambda(E, basis.N, _dptr(verts), _np_arg(basis.xi), _np_arg(basis.w), prec,
                                 _dptr(lam), _stream(stream)))
     return lam
 
@@ -321,7 +337,7 @@ def geom_factors(verts, basis: Basis, prec=AX_FP64, want_G=True, want_gwj=False,
     NP = (basis.N + 1) ** 3
     G = torch.empty((E, 6, NP), dtype=_prec_dtype(prec), device=verts.device) if want_G else None
     gwj = torch.empty((E, NP), dtype=torch.float64, device=verts.device) if want_gwj else None
-    _check(lib().ax_geom_factors(E, basis.N, _dptr(verts), _np_ptr(basis.xi), _np_ptr(basis.w), prec,
+    _check(lib().ax_geom_factors(E, basis.N, _dptr(verts), _np_arg(basis.xi), _np_arg(basis.w), prec,
                                  _dptr(G) if G is not None else None,
                                  _dptr(gwj) if gwj is not None else None, _stream(stream)))
     return G, gwj
@@ -332,8 +348,8 @@ def local_diag(geo, basis: Basis, geom=AX_TRILINEAR, stream=None):
     import torch
     E = geo.shape[0]
     out = torch.empty((E, (basis.N + 1) ** 3), dtype=torch.float64, device=geo.device)
-    _check(lib().ax_local_diag(E, basis.N, geom, _dptr(geo), _np_ptr(basis.D), _np_ptr(basis.xi),
-                               _np_ptr(basis.w), _dptr(out), _stream(stream)))
+    _check(lib().ax_local_diag(E, basis.N, geom, _dptr(geo), _np_arg(basis.D), _np_arg(basis.xi),
+                               _np_arg(basis.w), _dptr(out), _stream(stream)))
     return out
 
 
@@ -343,7 +359,7 @@ def check_mesh(verts, basis: Basis, stream=None):
     at a node; min_det is the smallest finite det J.  Other errors raise AxError."""
     bad = _i64(-1)
     dmin = ctypes.c_double(0.0)
-    code = lib().ax_check_mesh(verts.shape[0], basis.N, _dptr(verts), _np_ptr(basis.xi), ctypes.byref(bad),
+    code = lib().ax_check_mesh(verts.shape[0], basis.N, _dptr(verts), _np_arg(basis.xi), ctypes.byref(bad),
                                ctypes.byref(dmin), _stream(stream))
     if code not in (AX_OK, AX_ERR_ARG) or (code == AX_ERR_ARG and bad.value < 0):
         _check(code)
@@ -361,7 +377,7 @@ def node_coords(verts, basis: Basis, stream=None):
     import torch
     E = verts.shape[0]
     XYZ = torch.empty((E, 3, (basis.N + 1) ** 3), dtype=torch.float64, device=verts.device)
-    _check(lib().ax_node_coords(E, basis.N, _dptr(verts), _np_ptr(basis.xi), _dptr(XYZ), _stream(stream)))
+    _check(lib().ax_node_coords(E, basis.N, _dptr(verts), _np_arg(basis.xi), _dptr(XYZ), _stream(stream)))
     return XYZ
 
 
