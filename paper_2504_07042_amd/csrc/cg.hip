@@ -38,6 +38,9 @@ int batched_set_source(const ax_batch_plan* plan, void* ws, const void* xg, hipS
 // that are resident, each summing several elements per thread (4096 of them gave a vector of 10^6
 // one element per thread, and the scalar kernel twice the partials to read).
 constexpr int kRedBlocks = 2048;
+// The kernels that loop over tiles are held to the 64 VGPRs that keep all of them resident: at 68 the
+// last 256 work-groups of Q^T started when the others were done (11.4 million FP64 nodes: 120 us, 100
+// with all resident).
 constexpr int kRedThreads = 256;
 constexpr int kScalThreads = 1024;
 constexpr int kPoll = 8;         // iterations between host convergence checks
@@ -279,7 +282,7 @@ copy_pairs_kernel(CopyPair* __restrict__ cp, const int64_t* __restrict__ gptr, c
 #endif
 constexpr int kQtUnroll = AX_QT_UNROLL;
 template <typename T, bool FOLD>
-__global__ void __launch_bounds__(kRedThreads)
+__global__ void __launch_bounds__(kRedThreads, 8)
 qt_dot_kernel(int64_t n_global, const CopyPair* __restrict__ cp, const int32_t* __restrict__ gidx, int64_t n_local, const T* __restrict__ in,
               const T* __restrict__ pdir, T* __restrict__ out, double* __restrict__ partials,
               const double* __restrict__ epart, int64_t nparts)
