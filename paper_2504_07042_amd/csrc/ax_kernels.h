@@ -233,7 +233,7 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 
 // Waves per SIMD the register allocation of the prefetching (tile) kernel must allow: the most at
 // which a single-column kernel does not spill (a few registers at N1 = 4 and FP32 aside).  FP64:
-// four to N1 = 8, three above (natural use 110-168 VGPRs; 9 and 10 then run four), two for the
+// four to N1 = 8 (Helmholtz at N1 = 4 and 8: three, late_prefetch), three above (natural use 110-168 VGPRs; 9 and 10 then run four), two for the
 // Helmholtz form from N1 = 12 (184-224 VGPRs, 15-60 spills at three).  N1 = 16 is held to two by
 // its LDS.  FP32: five (96 VGPRs); the trilinear form to N1 = 12 and the Helmholtz form, four.
 #ifndef AX_MINW_F64_LO
@@ -249,7 +249,7 @@ constexpr int tile_waves(int N1, int geo, bool fp32)
 {
     if (N1 == 16) return 2;
     if (fp32) return geo == GEO_HELM || (geo == GEO_TRI && N1 <= 12) ? AX_MINW_F32_TRI : 5;
-    if (N1 <= 8) return geo == GEO_HELM && N1 == 4 ? 3 : AX_MINW_F64_LO;
+    if (N1 <= 8) return geo == GEO_HELM && (N1 == 4 || N1 == 8) ? 3 : AX_MINW_F64_LO;
     return geo == GEO_HELM && N1 >= 12 ? 2 : AX_MINW_F64_HI;
 }
 

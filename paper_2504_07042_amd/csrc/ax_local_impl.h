@@ -174,9 +174,14 @@ constexpr int s_hoist()
 // dead, so that the prefetched column adds nothing to the register peak (FP64 N1 = 12: 134 VGPRs
 // against 216 with the loads at the start of the item).  Parallelepipeds and stored factors up to
 // N1 = 8 fit the registers with the loads after the first contraction, which measured 2-5 % faster
-// there (a longer time in flight).
-template <int N1, int GEO>
-constexpr bool late_prefetch() { return is_trilinear(GEO) || N1 >= 9; }
+// there (a longer time in flight).  So does the FP64 Helmholtz form at N1 = 8 with three waves per SIMD:
+// 161 GDOF/s against 152 with the late loads at three or four.
+template <int N1, int GEO, typename T>
+constexpr bool late_prefetch()
+{
+    if (GEO == GEO_HELM && N1 == 8 && sizeof(T) == 8) return false;
+    return is_trilinear(GEO) || N1 >= 9;
+}
 template <int BLOCK>
 __device__ __forceinline__ void group_sync()
 {
@@ -410,7 +415,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     load_v(eb, vr);
     stage(xr, vr, true);
 
-    constexpr bool LATE = late_prefetch<N1, GEO>();
+    constexpr bool LATE = late_prefetch<N1, GEO, T>();
     TriCoefT<T> tc;
     while (eb < nblk) {
         const bool active = slot_active(eb);
