@@ -255,10 +255,10 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     constexpr int BLOCK = TL::BLOCK;
     constexpr int NV = is_trilinear(GEO) ? 24 : GEO == GEO_PARA ? 6 : 0;   // geometry words per element
     constexpr int VPT = (EPB * NV + BLOCK - 1) / BLOCK;          // and per thread
+    constexpr int NS = is_trilinear(GEO) ? kVertWords : NV;      // and staged
     __shared__ __attribute__((aligned(16))) T smem[L::WORDS];
-    // trilinear: the monomial coefficients of the map, [element][coordinate][monomial];
-    // parallelepiped: h
-    __shared__ __attribute__((aligned(16))) double svert[NV > 0 ? EPB * NV : 1];
+    // trilinear: the elements' vertex tables (vert_pos); parallelepiped: h
+    __shared__ __attribute__((aligned(16))) double svert[NS > 0 ? EPB * NS : 1];
     // (xi_k, w_k) pairs: the per-lane (xi_i, w_i), (xi_j, w_j) of the home columns, and xi_k, w_k
     // of the node loop for the kernels that do not keep them in scalar registers
     __shared__ double sxw[2 * N1];
@@ -374,7 +374,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
             }
 #pragma unroll
             for (int q = 0; q < VPT; ++q) {
-                // word idx of the table below: element idx / 24, coordinate, vertex
+                // element idx / 24, coordinate, vertex (vert_pos)
                 const int idx = tid + q * BLOCK, el = idx / 24, r24 = idx - 24 * el;
                 const int word = el * 24 + (r24 & 7) * 3 + (r24 >> 3);
                 dst[q] = *at_bytes(src, (uint32_t)((idx < EPB * 24 && word < lim ? word : 0) * 8));
@@ -400,11 +400,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
 #pragma unroll
                 for (int q = 0; q < VPT; ++q) {
                     const int idx = tid + q * BLOCK;
-                    // (a wave without vertex words skips the transform as a whole)
-                    if ((int)__builtin_amdgcn_readfirstlane(idx) < EPB * 24) {
-                        const double m = vertex_monomial(v[q], tid);
-                        if (idx < EPB * 24) svert[idx] = m;
-                    }
+                    if (idx < EPB * 24) svert[vert_pos(idx)] = v[q];
                 }
             }
         } else if constexpr (GEO == GEO_PARA) {
@@ -477,22 +473,14 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
             }
         }
         group_sync<BLOCK>();
-        // P2: x1 -> A; (per-element geometry invariants of the home column from the staged vertices)
+        // P2: x1 -> A
         if (inslot) {
 #pragma unroll
             for (int a = 0; a < N1; ++a) As[a * SJ] = o1[a];
         }
-        if constexpr (is_trilinear(GEO)) {
-            if (ONE || c == 0) {
-                const double* sv = svert + (inslot ? slot : 0) * 24;
-                TriCoef t64;
-                tri_prelude_monomial([&](int m, int q) { return sv[q * 8 + m]; }, sxw[2 * i], sxw[2 * j],
-                                     sxw[2 * i + 1], sxw[2 * j + 1], t64);
-                tri_narrow(t64, tc);
-            }
-        }
         group_sync<BLOCK>();
-        // P3: pointwise factors at the home column; r -> B, s -> A, t replaces x2 in registers
+        // P3: (per-element geometry invariants of the home column from the staged vertices,)
+        // pointwise factors at the home column; r -> B, s -> A, t replaces x2 in registers
         // (the idle lanes skip the stage: their column of x2 goes on as it is and is never stored)
         T ei = T(0);  // GATHER 2: this item's energy at the home column
         double h[GEO == GEO_PARA ? 6 : 1];
@@ -508,6 +496,15 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         const Buf bg(GEO == GEO_STORED || GEO == GEO_TRIL || GEO == GEO_HELM ? Gs + eb * (EPB * GF * NP) : nullptr);
         const uint32_t go = (uint32_t)(((active ? slot : 0) * GF * NP + i + j * N1) * (int)sizeof(T));
         if (inslot) {
+            if constexpr (is_trilinear(GEO)) {
+                if (ONE || c == 0) {
+                    const double* sv = svert + slot * kVertWords;
+                    TriCoef t64;
+                    tri_prelude([&](int v, int q) { return sv[q * 8 + v]; }, sxw[2 * i], sxw[2 * j], sxw[2 * i + 1],
+                                sxw[2 * j + 1], t64);
+                    tri_narrow(t64, tc);
+                }
+            }
             // the next node's x0, x1 are read before this node's results are written: the compiler
             // cannot tell the two fields' addresses apart and would keep the reads behind the writes
             T n0 = B[0], n1 = A[0];
@@ -634,7 +631,7 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
             });
         }
         // stage the next item: this lane's own home positions (read above by this lane only)
-        // and the vertex table (last read before the barriers of P3 and P4)
+        // and the vertex table (last read before the barrier of P4)
         stage(xn, vr, last_col);
 #pragma unroll
         for (int k = 0; k < N1; ++k) xr[k] = xn[k];

@@ -66,6 +66,11 @@ __device__ __forceinline__ void cross3(const double* a, const double* b, double*
 // Columns of 8J for the node column (r, s, :): col0 = a + t b, col1 = c + t d, col2 = u.
 // V(v, q) returns coordinate q of vertex v; it is called one coordinate at a time so that only
 // eight vertex words need to be live at once.
+// Neighbouring vertices are subtracted before anything is summed and opposite edges are blended, so
+// a short edge keeps its own accuracy beside long ones.  (The map's monomial coefficients would take
+// 18 multiply-adds per lane instead of these 84 operations, 0 to 5 % of the kernels' time, but have
+// the short edges as differences of long ones: on rotated boxes of aspect 10^4 an error of 1e-12 in
+// det J, against 4e-16.)
 template <typename VF>
 __device__ __forceinline__ void tri_columns(VF V, double r, double s, double* a, double* b, double* c,
                                             double* d, double* u)
@@ -115,63 +120,17 @@ __device__ __forceinline__ void tri_coefs(const double* a, const double* b, cons
     k.cw = 0.125 * wi * wj;
 }
 
+// Words per element of a vertex table in LDS, [coordinate][vertex] and two of padding, so that the
+// tables of consecutive elements start at different 16-byte slots of the 128 bytes the LDS serves per
+// clock.  Word idx = 8 (3 element + coordinate) + vertex of the elements' vertices stands at vert_pos(idx).
+constexpr int kVertWords = 26;
+__device__ __forceinline__ int vert_pos(int idx) { return idx + idx / 24 * (kVertWords - 24); }
+
 template <typename VF>
 __device__ __forceinline__ void tri_prelude(VF V, double r, double s, double wi, double wj, TriCoef& k)
 {
     double a[3], b[3], c[3], d[3], u[3];
     tri_columns(V, r, s, a, b, c, d, u);
-    tri_coefs(a, b, c, d, u, wi, wj, k);
-}
-
-// ---- The trilinear map in monomials ----
-//
-// 8 x(r,s,t) = sum over subsets m of {r, s, t} of M_m times the product of its variables (bit 0 of
-// m: r, bit 1: s, bit 2: t), so the columns of 8J for a node column (r, s, :) are
-//   a = M1 + M3 s,  b = M5 + M7 s,  c = M2 + M3 r,  d = M6 + M7 r,  u = M4 + M5 r + d s:
-// 18 multiply-adds per lane instead of the 84 operations of forming the 12 edge vectors and
-// blending them, from 21 words of the element instead of 24.
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x)
-{
-    typedef int i2 __attribute__((ext_vector_type(2)));
-    i2 v = __builtin_bit_cast(i2, x);
-    v.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, 0xf, 0xf, true);
-    v.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, v);
-}
-
-// The monomial coefficient M_v of one coordinate, v = lane % 8, from that coordinate of the
-// element's vertices 0..7 held by the 8 lanes (every lane of the wave active).  Differences are
-// taken first (against the first vertex of each half, which is exact for vertices within a factor
-// of two of each other), so nothing of the size of the coordinates is summed: the same accuracy
-// as from edge vectors.  M_0 (the mean) is not formed.
-__device__ __forceinline__ double vertex_monomial(double x, int lane)
-{
-    const double t = dpp_move<0x00>(x);                          // quad_perm 0,0,0,0: vertex 0 or 4
-    double w = x - t;
-    w = fma(dpp_move<0xB1>(w), (lane & 1) ? -1.0 : 1.0, w);       // lane ^ 1
-    w = fma(dpp_move<0x4E>(w), (lane & 2) ? -1.0 : 1.0, w);       // lane ^ 2
-    // lane ^ 4 = (lane ^ 7) ^ 3: row_half_mirror, then quad_perm 3,2,1,0
-    w = fma(dpp_move<0x1B>(dpp_move<0x141>(w)), (lane & 4) ? -1.0 : 1.0, w);
-    const double h = t - dpp_move<0x1B>(dpp_move<0x141>(t));      // lane 4: vertex 4 - vertex 0
-    return (lane & 7) == 4 ? fma(4.0, h, w) : w;
-}
-
-// Coefficients of the node column (r, s, :) from the monomials: M(m, q) is coordinate q of M_m.
-template <typename MF>
-__device__ __forceinline__ void tri_prelude_monomial(MF M, double r, double s, double wi, double wj, TriCoef& k)
-{
-    double a[3], b[3], c[3], d[3], u[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const double m3 = M(3, q), m5 = M(5, q), m7 = M(7, q);
-        a[q] = fma(m3, s, M(1, q));
-        b[q] = fma(m7, s, m5);
-        c[q] = fma(m3, r, M(2, q));
-        d[q] = fma(m7, r, M(6, q));
-        u[q] = fma(d[q], s, fma(m5, r, M(4, q)));
-    }
     tri_coefs(a, b, c, d, u, wi, wj, k);
 }
 

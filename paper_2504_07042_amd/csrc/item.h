@@ -47,9 +47,9 @@ struct BShape {
     static constexpr int NP = Shape<N1>::NP;
     static_assert(EPB * NT <= BLOCK && BLOCK % 64 == 0 && BLOCK <= 1024, "item shape");
     template <typename T>
-    static constexpr size_t field_bytes() { return ((size_t)TileLds<N1, EPB, sizeof(T)>::WORDS * sizeof(T) + 7) / 8 * 8; }
+    static constexpr size_t field_bytes() { return ((size_t)TileLds<N1, EPB, sizeof(T)>::WORDS * sizeof(T) + 15) / 16 * 16; }
     template <typename T>
-    static constexpr size_t lds_bytes() { return field_bytes<T>() + (size_t)EPB * 24 * 8; }
+    static constexpr size_t lds_bytes() { return field_bytes<T>() + (size_t)EPB * kVertWords * 8; }
 };
 
 // cs: source of the basis tables (CoefResident or CoefReload)
@@ -80,24 +80,19 @@ __device__ __forceinline__ void batched_item(const BMesh& m, int64_t eb, int nrh
     const T* X = reinterpret_cast<const T*>(m.X);
     T* Y = reinterpret_cast<T*>(m.Y);
 
-    // the monomial coefficients of each element's map, [element][coordinate][monomial]
-#pragma unroll
-    for (int g = 0; g < (EPB * 24 + S::BLOCK - 1) / S::BLOCK; ++g) {
-        const int q = tid + g * S::BLOCK;
-        if ((int)__builtin_amdgcn_readfirstlane(q) < EPB * 24) {
-            const int el = q / 24, r24 = q - 24 * el;
-            const int64_t off = (eb * EPB + el) * 24 + (r24 & 7) * 3 + (r24 >> 3);
-            const double mono = vertex_monomial(q < EPB * 24 && off < m.E * 24 ? m.verts[off] : 0.0, tid);
-            if (q < EPB * 24) svert[q] = mono;
-        }
+    // the elements' vertices
+    for (int q = tid; q < EPB * 24; q += S::BLOCK) {
+        const int el = q / 24, r24 = q - 24 * el;
+        const int64_t off = (eb * EPB + el) * 24 + (r24 & 7) * 3 + (r24 >> 3);
+        svert[vert_pos(q)] = off < m.E * 24 ? m.verts[off] : 0.0;
     }
     lds_barrier();
     TriCoefT<T> tc;
     if (inslot) {
-        const double* sv = svert + slot * 24;
+        const double* sv = svert + slot * kVertWords;
         const C b = cs.row();
         TriCoef t64;
-        tri_prelude_monomial([&](int mo, int q) { return sv[q * 8 + mo]; }, b.xi(i), b.xi(j), b.w(i), b.w(j), t64);
+        tri_prelude([&](int v, int q) { return sv[q * 8 + v]; }, b.xi(i), b.xi(j), b.w(i), b.w(j), t64);
         tri_narrow(t64, tc);
     }
     for (int c = 0; c < nrhs; ++c) {
