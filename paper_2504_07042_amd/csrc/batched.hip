@@ -249,6 +249,19 @@ static int order_variant(int N1, int prec)
     return item_has_alt(N1) ? t.item_alt : 0;
 }
 
+// The variants of a batch, var[N1].  The tile kernels take the nodes and weights as mirror-symmetric
+// and read half of them; an order whose tables are not runs its per-item kernel, which reads them all
+// (ax_local makes the same choice for a single mesh).
+static void order_variants(int n_mesh, const ax_problem* meshes, int prec, int* var)
+{
+    for (int N1 = 2; N1 <= kBMaxN1; ++N1) var[N1] = order_variant(N1, prec);
+    for (int q = 0; q < n_mesh; ++q) {
+        const int N1 = meshes[q].N + 1;
+        if (meshes[q].E > 0 && var[N1] >= kTileVariant && !symmetric_nodes(N1, meshes[q].xi, meshes[q].w))
+            var[N1] = item_has_alt(N1) ? tune_get(N1, TUNE_BATCHED, prec).item_alt : 0;
+    }
+}
+
 template <int N1, typename T, bool G>
 static int order_tile_launch(const char* ws, const BHeader& h, int64_t first, int64_t count, hipStream_t st)
 {
@@ -351,15 +364,15 @@ static int order_dispatch(int N1, int V, bool G, const char* ws, const BHeader& 
     }
 }
 
-// Work items of a batch: with the variants of `prec` (prec < 0: an upper bound over every
-// variant, for sizing a workspace before the precision is known).
-static int64_t n_items_of(int n_mesh, const ax_problem* meshes, int prec)
+// Work items of a batch with the variants `var` (null: an upper bound over every variant, for sizing a
+// workspace before the precision is known).
+static int64_t n_items_of(int n_mesh, const ax_problem* meshes, const int* var)
 {
     int64_t n = 0;
     for (int q = 0; q < n_mesh; ++q) {
         const int N1 = meshes[q].N + 1;
-        const int e = prec < 0 ? std::min({order_epb(N1, 0), order_epb(N1, 1), order_epb(N1, kTileVariant)})
-                               : order_epb(N1, order_variant(N1, prec));
+        const int e = var ? order_epb(N1, var[N1])
+                          : std::min({order_epb(N1, 0), order_epb(N1, 1), order_epb(N1, kTileVariant)});
         n += (meshes[q].E + e - 1) / e;
     }
     return n;
@@ -486,8 +499,8 @@ static int batched_noalloc(int n_mesh, const ax_problem* meshes, int nrhs, int p
                     kScratchMaxMeshes);
     AX_TRY(check_io(n_mesh, meshes, X, Y, col_stride));
     int var[kBMaxN1 + 1] = {};
-    for (int N1 = 2; N1 <= kBMaxN1; ++N1) var[N1] = order_variant(N1, prec);
-    const int64_t n_items = n_items_of(n_mesh, meshes, prec);
+    order_variants(n_mesh, meshes, prec, var);
+    const int64_t n_items = n_items_of(n_mesh, meshes, var);
     BHeader h{};
     layout(n_mesh, n_items, h);
     if ((size_t)h.bytes > kScratchBytes)
@@ -587,7 +600,7 @@ extern "C" int ax_batched_workspace_bytes(int n_mesh, const ax_problem* meshes, 
     AX_TRY(check_meshes(n_mesh, meshes));
     if (!bytes) return fail(AX_ERR_ARG, "bytes is NULL");
     BHeader h{};
-    layout(n_mesh, n_items_of(n_mesh, meshes, -1), h);
+    layout(n_mesh, n_items_of(n_mesh, meshes, nullptr), h);
     *bytes = (size_t)h.bytes;
     return AX_OK;
 }
@@ -624,8 +637,8 @@ static int batched_prepare(int n_mesh, const ax_problem* meshes, int nrhs, int p
     if (prec != AX_FP64 && prec != AX_FP32) return fail(AX_ERR_UNSUPPORTED, "batched precision must be FP64 or FP32");
     if (!workspace) return fail(AX_ERR_ARG, "workspace is NULL");
     if (!l2g) AX_TRY(check_io(n_mesh, meshes, X, Y, col_stride));
-    for (int N1 = 2; N1 <= kBMaxN1; ++N1) plan->order_variant[N1] = order_variant(N1, prec);
-    const int64_t n_items = n_items_of(n_mesh, meshes, prec);
+    order_variants(n_mesh, meshes, prec, plan->order_variant);
+    const int64_t n_items = n_items_of(n_mesh, meshes, plan->order_variant);
     BHeader h{};
     layout(n_mesh, n_items, h);
     if ((size_t)h.bytes > workspace_bytes) return fail(AX_ERR_NOMEM, "workspace of %lld bytes needed", (long long)h.bytes);
@@ -676,6 +689,7 @@ static int batched_prepare(int n_mesh, const ax_problem* meshes, int nrhs, int p
     if (!items.empty()) std::memcpy(host.data() + h.off_items, items.data(), sizeof(BItem) * items.size());
     // GLL tables of every order used, indexed by N1 - 2
     for (int q = 0; q < n_mesh; ++q) {
+        if (meshes[q].E == 0) continue;
         const int N1 = meshes[q].N + 1;
         if (prec == AX_FP64) {
             Basis<double> b;

@@ -101,3 +101,48 @@ def test_batched_validation(ax):
     p[0] = ax.AxProblem(4, 12, 0, 8, b.D.ctypes.data, b.xi.ctypes.data, b.w.ctypes.data, 0, None, None, None, None)
     n = ctypes.c_size_t()
     assert ax.lib().ax_batched_workspace_bytes(1, p, ctypes.byref(n)) == ax.AX_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("tile_alt", [0, 1])
+def test_batched_asymmetric_nodes(ax, prec, tile_alt):
+    """Tables whose nodes and weights are not mirror images (D stays a GLL one): the tile kernels read
+    half of such a table, so whatever the tuning table selects, the batch and ax_local use all of it."""
+    import torch
+    from paper_2504_07042_amd import autotune
+    P = ax.AX_FP64 if prec == "f64" else ax.AX_FP32
+    orders = range(1, 10)
+    saved = {N: autotune.tune_get(N, ax.AX_TUNE_BATCHED, P) for N in orders}
+    meshes, X, ref, env, fac = [], [], [], [], []
+    for N in orders:
+        m = meshgen.jittered_hex(3, 2, 2, alpha=0.15, seed=N)
+        b = ax.Basis(N)
+        b.w = b.w * np.linspace(0.9, 1.2, N + 1)
+        b.xi = b.xi + 0.02 * (1.0 - b.xi**2) + np.linspace(0.0, 0.01, N + 1)
+        x = meshgen.random_nodal(m.E, N, nrhs=2, seed=N)
+        meshes.append((torch.from_numpy(m.verts).cuda(), b))
+        X.append(torch.from_numpy(x).cuda().to(torch.float64 if prec == "f64" else torch.float32))
+        x = X[-1].double().cpu().numpy()
+        D = np.asarray(b.D).reshape(N + 1, N + 1)
+        G, _, _ = oracle.geom_factors(m.verts, N, b.xi, b.w)
+        ref.append(oracle.ax_local(D, G, x))
+        env.append(oracle.ax_envelope(D, G, x))
+        fac.append(fp32_bound(N, max_cond_j(m.verts, N)))
+    runs = {"single": [ax.ax_local(x, v, b, ax.AX_TRILINEAR, P) for x, (v, b) in zip(X, meshes)]}
+    try:
+        for N in orders:
+            autotune.tune_set(N, ax.AX_TUNE_BATCHED, P, kernel=ax.AX_KERNEL_TILE, tile_alt=tile_alt)
+        runs["plan"] = [torch.empty_like(x) for x in X]
+        ax.BatchedAxLocal(meshes, X, runs["plan"], P).launch()
+        runs["noalloc"] = [torch.empty_like(x) for x in X]
+        ax.batched_noalloc(meshes, X, runs["noalloc"], P)
+        torch.cuda.synchronize()
+    finally:
+        for N, s in saved.items():
+            autotune.tune_set(N, ax.AX_TUNE_BATCHED, P, **{k: s[k] for k in autotune.KNOBS})
+    for tag, Y in runs.items():
+        for q, y in enumerate(Y):
+            if prec == "f64":
+                check_fp64(y.cpu().numpy(), ref[q], env[q], tag=f"{tag} N={q + 1}")
+            else:
+                check_bound(y.cpu().numpy(), ref[q], env[q], fac[q], tag=f"{tag} N={q + 1}")
