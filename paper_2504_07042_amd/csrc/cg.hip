@@ -38,9 +38,9 @@ int batched_set_source(const ax_batch_plan* plan, void* ws, const void* xg, hipS
 // that are resident, each summing several elements per thread (4096 of them gave a vector of 10^6
 // one element per thread, and the scalar kernel twice the partials to read).
 constexpr int kRedBlocks = 2048;
-// The kernels that loop over tiles are held to the 64 VGPRs that keep all of them resident: at 68 the
-// last 256 work-groups of Q^T started when the others were done (11.4 million FP64 nodes: 120 us, 100
-// with all resident).
+// The kernels that loop over tiles are held to the 64 VGPRs that keep all of them resident (at 68 the
+// last 256 work-groups of Q^T started when the others were done).  None of them spills: the values
+// needed last (dinv) are loaded by the use of a tile and not before it.
 constexpr int kRedThreads = 256;
 constexpr int kScalThreads = 1024;
 constexpr int kPoll = 8;         // iterations between host convergence checks
@@ -402,17 +402,24 @@ update_dot_kernel(TX* __restrict__ x, T* __restrict__ r, const T* __restrict__ p
                     t.p[u] = p[o + g];
                     t.x[u] = x[o + g];
                 }
-                if (dinv) t.d[u] = dinv[g];
             }
         },
         [&](auto& t, int64_t q) {
+            if constexpr (XUPD) {
+                if (al != 0.0) {
+#pragma unroll
+                    for (int u = 0; u < t.U; ++u) x[o + q + u * kRedThreads] = (TX)((double)t.x[u] + al * (double)t.p[u]);
+                }
+            }
+            if (dinv) {
+#pragma unroll
+                for (int u = 0; u < t.U; ++u) t.d[u] = dinv[q + u * kRedThreads];
+            }
 #pragma unroll
             for (int u = 0; u < t.U; ++u) {
-                const int64_t g = q + u * kRedThreads;
                 if (al != 0.0) {
-                    if constexpr (XUPD) x[o + g] = (TX)((double)t.x[u] + al * (double)t.p[u]);
                     t.r[u] = (T)((double)t.r[u] - al * (double)t.ap[u]);
-                    r[o + g] = t.r[u];
+                    r[o + q + u * kRedThreads] = t.r[u];
                 }
                 acc = fma((double)t.r[u], (double)t.r[u], acc);
                 if (dinv) acz = fma((double)t.r[u] * (double)t.d[u], (double)t.r[u], acz);
@@ -485,11 +492,14 @@ cg_dir_kernel(TX* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, Cg
                 const int64_t g = q + u * kRedThreads;
                 t.p[u] = p[o + g];
                 t.r[u] = r[o + g];
-                if (dinv) t.d[u] = dinv[g];
                 if constexpr (XUPD) t.x[u] = x[o + g];
             }
         },
         [&](auto& t, int64_t q) {
+            if (dinv) {
+#pragma unroll
+                for (int u = 0; u < t.U; ++u) t.d[u] = dinv[q + u * kRedThreads];
+            }
 #pragma unroll
             for (int u = 0; u < t.U; ++u) {
                 const int64_t g = q + u * kRedThreads;
