@@ -349,6 +349,14 @@ qt_dot_kernel(int64_t n_global, const CopyPair* __restrict__ cp, const int32_t* 
     if (threadIdx.x == 0) partials[c * kRedBlocks + blockIdx.x] = v[0];
 }
 
+// Among several columns the finished ones move no data until the slowest is done (FP64, N = 7, 24^3, 5
+// of 6 columns finished: 89 ms for 200 iterations, 127 with their vectors read).  A single column
+// goes on without the test, which its loads would wait for, up to the next look of the host.
+__device__ __forceinline__ bool column_finished(int converged, int breakdown)
+{
+    return gridDim.y > 1 && (converged || breakdown);
+}
+
 // The work-group's sums of acc (r . r) and, with `pre`, acz (r . z) into its partials.
 __device__ __forceinline__ void store_partials(double acc, double acz, bool pre, double* __restrict__ partials)
 {
@@ -384,6 +392,16 @@ update_dot_kernel(TX* __restrict__ x, T* __restrict__ r, const T* __restrict__ p
                   double* __restrict__ partials)
 {
     const int c = blockIdx.y;
+    if (column_finished(sc[c].converged, sc[c].breakdown)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            CgScal& q = sc[c];
+            q.alpha = 0.0;
+            q.mid_rz = q.rz;
+            q.mid_converged = q.converged;
+            q.mid_breakdown = q.breakdown;
+        }
+        return;
+    }
     const int64_t o = (int64_t)c * n;
     double al = 0.0, acc = 0.0, acz = 0.0;
     each_tile<UpdateRegs<TX, T>::template Of>(
@@ -476,6 +494,14 @@ cg_dir_kernel(TX* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, Cg
               const T* __restrict__ dinv, const double* __restrict__ partials)
 {
     const int c = blockIdx.y;
+    if (column_finished(sc[c].mid_converged, sc[c].mid_breakdown)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            sc[c].beta = 0.0;
+            sc[c].converged = sc[c].mid_converged;
+            sc[c].breakdown = sc[c].mid_breakdown;
+        }
+        return;
+    }
     const int64_t o = (int64_t)c * n;
     const double al = XUPD ? sc[c].alpha : 0.0;
     double be = 0.0;

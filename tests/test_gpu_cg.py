@@ -321,3 +321,29 @@ def test_cg_tile_edges(ax, grid, nrhs, jacobi):
     # iterations times 2^-53 times the growth of the iterates, below 1e-12 here)
     r = b - prob.apply(x)
     assert float((r.norm(dim=1) / b.norm(dim=1)).max()) <= 2e-10
+
+
+# Columns that are finished at the start (zero right-hand sides) or early take no further part in the
+# vector kernels; the others go on as if alone.  The second grid moves the x update into the direction
+# kernel (vectors above 64 MiB).
+@pytest.mark.parametrize("N,grid,jacobi,inner", [(3, (4, 3, 5), False, "fp64"), (3, (4, 3, 5), True, "fp64"),
+                                                 (2, (5, 4, 3), True, "fp32"), (1, (100, 120, 130), True, "fp64")])
+def test_cg_finished_columns(ax, N, grid, jacobi, inner):
+    import torch
+    m = meshgen.jittered_hex(*grid, alpha=0.1, seed=6)
+    l2g, ng, mask = meshgen.global_numbering(*grid, N)
+    prob = ax.Problem(torch.from_numpy(m.verts).cuda(), ax.Basis(N), ax.GatherScatter(l2g, ng, mask))
+    free = ~torch.from_numpy(np.asarray(mask)).cuda().bool()
+    g = torch.Generator("cuda").manual_seed(3)
+    b = (torch.rand((6, ng), dtype=torch.float64, device="cuda", generator=g) - 0.5) * free
+    b[0] = b[3] = 0.0
+    x0 = torch.zeros_like(b)
+    kw = dict(rtol=1e-10, precond=ax.AX_PRECOND_JACOBI if jacobi else ax.AX_PRECOND_NONE)
+    if inner == "fp32":
+        kw.update(inner_prec=ax.AX_FP32, inner_rtol=0.1, max_outer=60, refine=ax.AX_REFINE_RELIABLE)
+    x0[1] = ax.cg_solve(prob, b[1:2], **kw)[0]      # starts at its solution
+    x, rep = ax.cg_solve(prob, b, x=x0.clone(), **kw)
+    assert rep["status"] == "AX_OK", rep
+    assert torch.equal(x[0], x0[0]) and torch.equal(x[3], x0[3])
+    r = b - prob.apply(x)
+    assert float((r.norm(dim=1) / b.norm(dim=1).clamp_min(1e-300)).max()) <= 2e-10
