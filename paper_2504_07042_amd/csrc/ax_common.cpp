@@ -128,7 +128,7 @@ extern "C" int ax_tune_get(int N, int kind, int prec, ax_tune* t)
     } else {
         t->elems_per_group = tile_epb(N1, kind != TUNE_BATCHED && e.tile_alt != 0);
         t->block = ((t->elems_per_group * N1 * N1 + 63) / 64) * 64;
-        t->waves = tile_waves(N1, geo, fp32);
+        t->waves = tile_waves(N1, geo, fp32, kind != TUNE_BATCHED);
     }
     return AX_OK;
 }

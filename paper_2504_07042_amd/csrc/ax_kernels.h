@@ -231,26 +231,27 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
     }
 }
 
-// Waves per SIMD the register allocation of the prefetching (tile) kernel must allow: the most at
-// which a single-column kernel does not spill (a few registers at N1 = 4 and FP32 aside).  FP64:
-// four to N1 = 8 (Helmholtz at N1 = 4 and 8: three, late_prefetch), three above (natural use 110-168 VGPRs; 9 and 10 then run four), two for the
-// Helmholtz form from N1 = 12 (184-224 VGPRs, 15-60 spills at three).  N1 = 16 is held to two by
-// its LDS.  FP32: five (96 VGPRs); the trilinear form to N1 = 12 and the Helmholtz form, four.
-#ifndef AX_MINW_F64_LO
-#define AX_MINW_F64_LO 4
-#endif
-#ifndef AX_MINW_F64_HI
-#define AX_MINW_F64_HI 3
-#endif
-#ifndef AX_MINW_F32_TRI
-#define AX_MINW_F32_TRI 4
-#endif
-constexpr int tile_waves(int N1, int geo, bool fp32)
+// Waves per SIMD the register allocation of the prefetching (tile) kernel must allow, by its form and,
+// for the trilinear forms, by whether it is the single-column kernel (`one`) or keeps the factor
+// coefficients between columns (17 values more).  Chosen by timing every budget on every form (2^23.6
+// nodes; in brackets the time against one wave more or, where given, fewer).
+//   FP64: four to N1 = 8 and three above (natural use 110-168 VGPRs).  One fewer for the Helmholtz form
+// at N1 = 4 (0.89), 7 (0.90; columns 0.88) and 8 (late_prefetch), and for its columns at N1 = 11 (0.84,
+// 26 spills at three); two for it from N1 = 13 and for columns at 12 (184-224 VGPRs; at three 1.2 to 2.3
+// times the time); two at N1 = 15, whose LDS admits no third group (stored factors 0.92, trilinear
+// columns 0.91, partial 0.88).  At N1 = 10, 13 and 14 some forms spill 4 to 19 at three and are no slower.
+//   FP32: five (96 VGPRs); four for the trilinear form to N1 = 12, the Helmholtz form, stored factors at
+// N1 = 8 (0.96; two columns 0.89) and partial columns at N1 = 2 (0.81), 8 (0.70, 22 spills at five) and 11
+// (0.87); three for columns of the Helmholtz form at N1 = 11 and 12 (0.83) and the partial one at 12 (0.89).
+constexpr int tile_waves(int N1, int geo, bool fp32, bool one)
 {
-    if (N1 == 16) return 2;
-    if (fp32) return geo == GEO_HELM || (geo == GEO_TRI && N1 <= 12) ? AX_MINW_F32_TRI : 5;
-    if (N1 <= 8) return geo == GEO_HELM && (N1 == 4 || N1 == 8) ? 3 : AX_MINW_F64_LO;
-    return geo == GEO_HELM && N1 >= 12 ? 2 : AX_MINW_F64_HI;
+    if (fp32) {
+        if (!one && ((geo == GEO_HELM && (N1 == 11 || N1 == 12)) || (geo == GEO_TRIL && N1 == 12))) return 3;
+        if (geo == GEO_HELM || (geo == GEO_TRI && N1 <= 12) || (geo == GEO_STORED && N1 == 8)) return 4;
+        return !one && geo == GEO_TRIL && (N1 == 2 || N1 == 8 || N1 == 11) ? 4 : 5;
+    }
+    if (geo == GEO_HELM) return N1 >= 13 || (!one && N1 >= 11) ? 2 : N1 == 4 || N1 >= 7 ? 3 : 4;
+    return N1 <= 8 ? 4 : N1 == 15 ? 2 : 3;
 }
 
 // Coefficient sources of the contractions.  CoefResident reads the basis tables as they are

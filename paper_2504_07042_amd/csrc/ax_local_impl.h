@@ -659,16 +659,10 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
     }
 }
 
-template <int N1, int GEO, typename T>
-constexpr int min_waves()
-{
-    return tile_waves(N1, GEO, sizeof(T) == 4);
-}
-
 // ONE: a single column (nrhs = 1), so that the per-column factor coefficients die with the
 // pointwise stage instead of living through the item for the next column.
 template <int N1, int GEO, bool EO, int GATHER, int EPBX, bool ONE, typename T>
-__global__ void __launch_bounds__((Tile<N1, EPBX>::BLOCK), (min_waves<N1, GEO, T>()))
+__global__ void __launch_bounds__((Tile<N1, EPBX>::BLOCK), (tile_waves(N1, GEO, sizeof(T) == 4, ONE)))
 ax_local_kernel(const AxArgs<T> ka)
 {
     if constexpr (reload_coefs<N1, EO, T>() || use_dpp<N1, GEO, EO, ONE, T>())

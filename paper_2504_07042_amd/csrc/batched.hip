@@ -113,7 +113,7 @@ struct MeshListWalk {
 // of the single-mesh launches (one item ahead, across meshes), for the orders whose batched
 // tuning entry asks for it (kernel = TILE).
 template <int N1, typename T, bool G>
-__global__ void __launch_bounds__((Tile<N1, Shape<N1>::EPB>::BLOCK), (min_waves<N1, GEO_TRI, T>()))
+__global__ void __launch_bounds__((Tile<N1, Shape<N1>::EPB>::BLOCK), (tile_waves(N1, GEO_TRI, sizeof(T) == 4, false)))
 order_tile_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ meshes, int64_t n, int nrhs,
                   const Basis<T>* __restrict__ bsp)
 {
@@ -140,7 +140,7 @@ struct MeshSliceWalk {
 // stays live over an item, so the kernel has the single-mesh kernel's register footprint at every
 // order (the list form spills at FP64 N1 >= 8).
 template <int N1, typename T, bool G>
-__global__ void __launch_bounds__((Tile<N1, Shape<N1>::EPB>::BLOCK), (min_waves<N1, GEO_TRI, T>()))
+__global__ void __launch_bounds__((Tile<N1, Shape<N1>::EPB>::BLOCK), (tile_waves(N1, GEO_TRI, sizeof(T) == 4, false)))
 order_slice_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ meshes, int nrhs,
                    const Basis<T>* __restrict__ bsp)
 {
