@@ -239,7 +239,9 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 // at N1 = 4 (0.89), 7 (0.90; columns 0.88) and 8 (late_prefetch), and for its columns at N1 = 11 (0.84,
 // 26 spills at three); two for it from N1 = 13 and for columns at 12 (184-224 VGPRs; at three 1.2 to 2.3
 // times the time); two at N1 = 15, whose LDS admits no third group (stored factors 0.92, trilinear
-// columns 0.91, partial 0.88).  At N1 = 10, 13 and 14 some forms spill 4 to 19 at three and are no slower.
+// columns 0.91, partial 0.88), and at 16; stored factors there at one, whose LDS still admits two groups, so
+// that the compiler holds a column's 96 factor loads in flight (248 VGPRs, 168 at two: 0.92 with two columns).
+// At N1 = 10, 13 and 14 some forms spill 4 to 19 at three and are no slower.
 //   FP32: five (96 VGPRs); four for the trilinear form to N1 = 12, the Helmholtz form, stored factors at
 // N1 = 8 (0.96; two columns 0.89) and partial columns at N1 = 2 (0.81), 8 (0.70, 22 spills at five) and 11
 // (0.87); three for columns of the Helmholtz form at N1 = 11 and 12 (0.83) and the partial one at 12 (0.89).
@@ -251,7 +253,7 @@ constexpr int tile_waves(int N1, int geo, bool fp32, bool one)
         return !one && geo == GEO_TRIL && (N1 == 2 || N1 == 8 || N1 == 11) ? 4 : 5;
     }
     if (geo == GEO_HELM) return N1 >= 13 || (!one && N1 >= 11) ? 2 : N1 == 4 || N1 >= 7 ? 3 : 4;
-    return N1 <= 8 ? 4 : N1 == 15 ? 2 : 3;
+    return N1 <= 8 ? 4 : N1 <= 14 ? 3 : geo == GEO_STORED && N1 == 16 ? 1 : 2;
 }
 
 // Coefficient sources of the contractions.  CoefResident reads the basis tables as they are
