@@ -42,8 +42,9 @@ DEFAULT = {"kernel": AX_KERNEL_AUTO, "tile_alt": 0, "item_alt": 0, "waves_alt": 
 GRID_MULTS = (1, 2, 4, 8)
 MARGIN = 0.01      # a variant replaces the default only if it is this much faster
 KERNEL_MARGIN = 0.10   # single-mesh forms: another kernel than the default's, only if this much faster
-                       # than the default kernel's best variant (between the two kernels repeat runs
-                       # differ by up to 8 % at the orders where they tie)
+                       # than the default kernel's best variant (at the orders where the two tie, repeat
+                       # runs differ by up to 8 %; FP64 N = 6, where the tile kernel leads by 1 to 8 %,
+                       # keeps its per-item default by this)
 
 
 # The sources the tuned launches depend on: the AxLocal kernels (tile, per-item, batched), their

@@ -68,8 +68,10 @@ constexpr int item_waves(int N1, bool fp32, bool partial, int alt)
 
 // Which kernel runs when the tuning table says "auto" (measured on gfx950, GDOF/s at 2^24 nodes,
 // tile against per-item kernel).  The tile kernel (FP64 N1 = 6: 200 against 190; 9: 203, 177; 10:
-// 181, 161; FP32 9: 304, 305; 13: 274, 274; 15: 279, 268; partial form 13: 286, 282) except FP64 N1 = 7, full form, where
-// repeat runs put them 3 to 8 % apart (205-210, 194-200).
+// 181, 161; FP32 9: 304, 305; 13: 274, 274; 15: 279, 268; partial form 13: 286, 282) except FP64
+// N1 = 7, full form: the per-item kernel is that order's documented default, kept although the tile
+// kernel is now the faster one there (us at 2^22.9, 2^23.6 and 2^24 nodes: 41.6, 59.7, 79.3 against
+// 41.9, 63.1, 86.2); the table's kernel field selects it.
 constexpr bool item_default(int N1, int geo, bool fp32) { return geo == GEO_TRI && !fp32 && N1 == 7; }
 
 // Orders with a batched tile kernel (the single-mesh tile body walking the batch's work list):
@@ -281,8 +283,6 @@ struct CoefResident {
     __device__ __forceinline__ T M(int q) const { return b.M[q]; }
     __device__ __forceinline__ T Cm(int q) const { return b.Cm[q]; }
     __device__ __forceinline__ T Rm(int q) const { return b.Rm[q]; }
-    __device__ __forceinline__ double xi(int q) const { return b.xi[q]; }
-    __device__ __forceinline__ double w(int q) const { return b.w[q]; }
 };
 
 template <typename KA>
@@ -356,8 +356,6 @@ struct CoefConst {
     __device__ __forceinline__ T M(int q) const { return k->M[q]; }
     __device__ __forceinline__ T Cm(int q) const { return k->Cm[q]; }
     __device__ __forceinline__ T Rm(int q) const { return k->Rm[q]; }
-    __device__ __forceinline__ double xi(int q) const { return k->xi[q]; }
-    __device__ __forceinline__ double w(int q) const { return k->w[q]; }
 };
 
 // ---- FP64 contractions with row-broadcast coefficients ----
@@ -633,12 +631,6 @@ __device__ __forceinline__ void contract(const C& src, const T* in, T* out)
         contract_eo<N1, TRANS>(src, in, out);
     else
         contract_full<N1, TRANS>(src, in, out);
-}
-
-template <int N1, bool TRANS, bool EO, typename T>
-__device__ __forceinline__ void contract(const Basis<T>& bs, const T* in, T* out)
-{
-    contract<N1, TRANS, EO>(CoefResident<T>{bs}, in, out);
 }
 
 }  // namespace ax

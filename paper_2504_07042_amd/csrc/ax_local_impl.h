@@ -61,10 +61,12 @@ struct AxArgs {
 };
 
 // FP64 kernels whose even-odd tables are held in vector registers and broadcast (contract_dpp):
-// the orders whose tables overflow the scalar registers (N1 >= 9), and the multi-column trilinear
-// kernels at N1 = 4 and 8, which spill with scalar tables (30 and 99 VGPRs at four waves per SIMD,
-// none with broadcast ones).  Elsewhere the scalar tables are the faster source: no accumulator
-// has to be cleared first (one move per output, 6 % of the vector work at N1 = 8).
+// the orders whose tables overflow the scalar registers (N1 >= 9), and among the trilinear kernels
+// N1 = 8 and the multi-column ones at N1 = 4, which spill with scalar tables (99 and 30 VGPRs with
+// several columns, 12 to 82 scalar registers with one; none with broadcast ones.  One column, N = 7,
+// broadcast / scalar tables in us at 2^24 nodes: trilinear 74.8 / 73.1, at 2^22.9 39.9 / 40.7;
+// partial 84 / 96; Helmholtz 104 / 378).  Elsewhere the scalar tables are the faster source: no
+// accumulator has to be cleared first (one move per output, 6 % of the vector work at N1 = 8).
 template <int N1, int GEO, bool EO, bool ONE, typename T>
 constexpr bool use_dpp()
 {

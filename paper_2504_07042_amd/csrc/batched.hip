@@ -120,8 +120,7 @@ order_tile_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ mes
     constexpr int EPB = Shape<N1>::EPB, NP = N1 * N1 * N1;
     static_assert(batched_tile_available(N1, sizeof(T) == 4), "no batched tile kernel at this order");
     const MeshListWalk<EPB, NP> wl{items, meshes, n};
-    // constant memory: a plain reference has the tables of the node loop and of the contractions read
-    // again after every store (FP64 N1 = 8, 8 columns: 223 GDOF/s, 262 with this)
+    // constant memory (order_slice_kernel)
     const auto& bs = *as_constant(bsp);
     ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, false, T>(0, nrhs, nullptr, nullptr, nullptr, nullptr, bs, nullptr, 0,
                                                          NP, 0, nullptr, CoefConst<T>{&bs}, wl);
@@ -149,7 +148,7 @@ order_slice_kernel(const BItem* __restrict__ items, const BMesh* __restrict__ me
     const BMesh m = meshes[sl.mesh];
     const MeshSliceWalk wl{sl.eb, m.wgs};
     // constant memory: a plain reference has the tables of the node loop and of the contractions read
-    // again after every store (FP64 N1 = 8, 8 columns: 223 GDOF/s, 262 with this)
+    // again after every store (FP64 N1 = 8, 8 columns: 223 GDOF/s, 264 with this)
     const auto& bs = *as_constant(bsp);
     ax_local_body<N1, GEO_TRI, true, G ? 1 : 0, EPB, false, T>(m.E, nrhs, m.verts, nullptr, static_cast<const T*>(m.X),
                                                          static_cast<T*>(m.Y), bs, G ? m.l2g : nullptr, m.ldg, NP, m.ld,

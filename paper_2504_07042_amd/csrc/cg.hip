@@ -51,7 +51,6 @@ struct CgScal {
     double rr;      // r . r (convergence test on the residual norm)
     double rz;      // r . z, z = M^-1 r (= r . r without a preconditioner)
     double alpha;
-    double beta;
     double tol2;    // (rtol * |b|)^2 target on r . r
     int converged;  // 1 once r . r <= tol2
     int breakdown;  // 1 on p^T A p <= 0 or a non-finite scalar
@@ -160,7 +159,7 @@ __device__ __forceinline__ void sum_partials(const double* partials, const doubl
 }
 
 // mode 0: rr = sum (initial), converged if rr <= tol2.
-// mode 3: rr = sum after a reliable update (alpha, beta and the iteration count are kept).
+// mode 3: rr = sum after a reliable update (alpha and the iteration count are kept).
 // mode 4: sum = d . d of the iterate about to be folded; flags a non-finite one (breakdown 2).
 // With `pre` the partials hold r . r in the first and r . z in the second part (modes 0, 3);
 // without, r . z = r . r.
@@ -179,7 +178,7 @@ cg_scalar_kernel(const double* __restrict__ partials, CgScal* __restrict__ sc, i
         q.converged = (s <= q.tol2) ? 1 : 0;
         q.breakdown = isfinite(s) && isfinite(s2) ? 0 : 1;
         q.iters = 0;
-        q.alpha = q.beta = 0.0;
+        q.alpha = 0.0;
     } else if (mode == 4) {
         // s = d . d of the reduced-precision iterate: a non-finite one must not reach x
         if (!isfinite(s)) q.breakdown = 2;
@@ -232,7 +231,6 @@ __device__ __forceinline__ bool cg_beta(const double* partials, CgScal* q, int c
         else if (s <= q->tol2) converged = 1;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        q->beta = beta;
         q->converged = converged;
         q->breakdown = breakdown;
         if (step) {
@@ -496,7 +494,6 @@ cg_dir_kernel(TX* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, Cg
     const int c = blockIdx.y;
     if (column_finished(sc[c].mid_converged, sc[c].mid_breakdown)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            sc[c].beta = 0.0;
             sc[c].converged = sc[c].mid_converged;
             sc[c].breakdown = sc[c].mid_breakdown;
         }
