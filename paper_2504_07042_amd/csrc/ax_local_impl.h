@@ -497,6 +497,17 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
         constexpr int GF = GEO == GEO_STORED ? 6 : GEO == GEO_HELM ? 2 : 1;
         const Buf bg(GEO == GEO_STORED || GEO == GEO_TRIL || GEO == GEO_HELM ? Gs + eb * (EPB * GF * NP) : nullptr);
         const uint32_t go = (uint32_t)(((active ? slot : 0) * GF * NP + i + j * N1) * (int)sizeof(T));
+        // FP64: the scales of the next four nodes in flight (the empty asm keeps their loads from moving back
+        // to their use).  Left to the scheduler some of these kernels wait for every node's scale in turn
+        // (Helmholtz N = 8, two columns: 185 us, 163 like this; partial N = 6, two columns: 1.15 times; the
+        // others within 5 % either way).  In FP32 it gains nothing (0.93 to 1.03).
+        constexpr bool AHEAD = (GEO == GEO_TRIL || GEO == GEO_HELM) && sizeof(T) == 8;
+        constexpr int LQ = N1 < 4 ? N1 : 4;
+        T lq[AHEAD ? LQ : 1];
+        if constexpr (AHEAD) {
+            each_node<LQ>([&](auto k) { lq[k] = bg.template load<k * NT * (int)sizeof(T), T>(go); });
+            asm volatile("");
+        }
         if (inslot) {
             if constexpr (is_trilinear(GEO)) {
                 if (ONE || c == 0) {
@@ -534,7 +545,14 @@ ax_local_body(int64_t E, int nrhs, const double* __restrict__ geo, const T* __re
                 } else if constexpr (GEO == GEO_TRIL || GEO == GEO_HELM) {
                     T tk, wk;
                     node_xw<N1, GEO, EO>(bs, sxw, k, tk, wk);
-                    const T lam = bg.template load<k * NT * (int)sizeof(T), T>(go);
+                    T lam;
+                    if constexpr (AHEAD) {
+                        lam = lq[k % LQ];
+                        if constexpr (k + LQ < N1) lq[k % LQ] = bg.template load<(k + LQ) * NT * (int)sizeof(T), T>(go);
+                        asm volatile("");
+                    } else {
+                        lam = bg.template load<k * NT * (int)sizeof(T), T>(go);
+                    }
                     tri_adj_k<T>(tc, tk, g);
                     x0 *= lam;
                     x1 *= lam;
