@@ -244,14 +244,16 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 // columns 0.91, partial 0.88), and at 16; stored factors there at one, whose LDS still admits two groups, so
 // that the compiler holds a column's 96 factor loads in flight (248 VGPRs, 168 at two: 0.92 with two columns).
 // At N1 = 10, 13 and 14 some forms spill 4 to 19 at three and are no slower.
-//   FP32: five (96 VGPRs); four for the trilinear form to N1 = 12, the Helmholtz form, stored factors at
+//   FP32: five (96 VGPRs); four for the trilinear form to N1 = 12 (single columns at N1 = 4 and 8 fit
+// five: 0.95, 0.97), the Helmholtz form, stored factors at
 // N1 = 8 (0.96; two columns 0.89) and partial columns at N1 = 2 (0.81), 8 (0.70, 22 spills at five) and 11
 // (0.87); three for columns of the Helmholtz form at N1 = 11 and 12 (0.83) and the partial one at 12 (0.89).
 constexpr int tile_waves(int N1, int geo, bool fp32, bool one)
 {
     if (fp32) {
         if (!one && ((geo == GEO_HELM && (N1 == 11 || N1 == 12)) || (geo == GEO_TRIL && N1 == 12))) return 3;
-        if (geo == GEO_HELM || (geo == GEO_TRI && N1 <= 12) || (geo == GEO_STORED && N1 == 8)) return 4;
+        if (geo == GEO_HELM || (geo == GEO_STORED && N1 == 8)) return 4;
+        if (geo == GEO_TRI) return N1 <= 12 && !(one && (N1 == 4 || N1 == 8)) ? 4 : 5;
         return !one && geo == GEO_TRIL && (N1 == 2 || N1 == 8 || N1 == 11) ? 4 : 5;
     }
     if (geo == GEO_HELM) return N1 >= 13 || (!one && N1 >= 11) ? 2 : N1 == 4 || N1 >= 7 ? 3 : 4;
