@@ -243,11 +243,12 @@ __device__ __forceinline__ void rpencil_write(T* F, const T* o)
 // times the time); two at N1 = 15, whose LDS admits no third group (stored factors 0.92, trilinear
 // columns 0.91, partial 0.88), and at 16; stored factors there at one, whose LDS still admits two groups, so
 // that the compiler holds a column's 96 factor loads in flight (248 VGPRs, 168 at two: 0.92 with two columns).
-// At N1 = 10, 13 and 14 some forms spill 4 to 19 at three and are no slower.
+// At N1 = 10, 12, 13 and 14 some forms spill 4 to 19 at three and are no slower.
 //   FP32: five (96 VGPRs); four for the trilinear form to N1 = 12 (single columns at N1 = 4 and 8 fit
-// five: 0.95, 0.97), the Helmholtz form, stored factors at
-// N1 = 8 (0.96; two columns 0.89) and partial columns at N1 = 2 (0.81), 8 (0.70, 22 spills at five) and 11
-// (0.87); three for columns of the Helmholtz form at N1 = 11 and 12 (0.83) and the partial one at 12 (0.89).
+// five: 0.97, 0.97 to 1.0; at N1 = 10 five spills 8 and is 1-3 % faster from 2^23.6 nodes, 6 % slower below
+// 2^22), the Helmholtz form, stored factors at N1 = 8 (0.96; two columns 0.89) and partial columns at N1 = 2
+// (0.81), 8 (0.70, 22 spills at five) and 11 (0.87); three for columns of the Helmholtz form at N1 = 11 and
+// 12 (0.83) and the partial one at 12 (0.89).
 constexpr int tile_waves(int N1, int geo, bool fp32, bool one)
 {
     if (fp32) {
